@@ -201,17 +201,13 @@ __device__ __forceinline__ void row_qparams(float mn, float mx, float& s, float&
   inv = rc;
 }
 
-// Code of x: clamp(round(x / s) + z, 0, 255), computed as round(x * (1/s) + z).
-__device__ __forceinline__ float quant_code(float x, float inv, float z) {
-  return __builtin_amdgcn_fmed3f(rintf(fmaf(x, inv, z)), 0.0f, 255.0f);
-}
-
-// Four codes (already integral in [0, 255]) packed little-endian into a word.
-__device__ __forceinline__ uint32_t pack_codes4(float c0, float c1, float c2, float c3) {
-  uint32_t w = __builtin_amdgcn_cvt_pk_u8_f32(c0, 0, 0u);
-  w = __builtin_amdgcn_cvt_pk_u8_f32(c1, 1, w);
-  w = __builtin_amdgcn_cvt_pk_u8_f32(c2, 2, w);
-  return __builtin_amdgcn_cvt_pk_u8_f32(c3, 3, w);
+// Codes of four values, clamp(round(x / s) + z, 0, 255), packed little-endian
+// into a word: v_cvt_pk_u8_f32 rounds half to even and saturates by itself.
+__device__ __forceinline__ uint32_t quant_codes4(const float* x, float inv, float z) {
+  uint32_t w = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(x[0], inv, z), 0, 0u);
+  w = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(x[1], inv, z), 1, w);
+  w = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(x[2], inv, z), 2, w);
+  return __builtin_amdgcn_cvt_pk_u8_f32(fmaf(x[3], inv, z), 3, w);
 }
 
 // -------------------------------------- paper low tier (App. A.1, Eq. 17)
@@ -535,12 +531,7 @@ __device__ __forceinline__ void encode_row(const float* x, int r, int k_hi, int 
     group_qparams_f16(mn, mx, s16, z16, inv);
     uint32_t w[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      uint32_t c = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(y[4 * j], inv, z16), 0, 0u);
-      c = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(y[4 * j + 1], inv, z16), 1, c);
-      c = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(y[4 * j + 2], inv, z16), 2, c);
-      w[j] = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(y[4 * j + 3], inv, z16), 3, c);
-    }
+    for (int j = 0; j < 4; ++j) w[j] = quant_codes4(y + 4 * j, inv, z16);
     const int l = r - k_hi;
     store_words<16>(codes + static_cast<size_t>(l) * D + col0, w);
     if ((cg & 1) == 0)
@@ -572,8 +563,7 @@ __device__ __forceinline__ void encode_row(const float* x, int r, int k_hi, int 
     uint32_t w[CPT / 4];
 #pragma unroll
     for (int j = 0; j < CPT / 4; ++j)
-      w[j] = pack_codes4(quant_code(x[4 * j], inv, z), quant_code(x[4 * j + 1], inv, z),
-                         quant_code(x[4 * j + 2], inv, z), quant_code(x[4 * j + 3], inv, z));
+      w[j] = quant_codes4(x + 4 * j, inv, z);
     const int l = r - k_hi;
     store_words<CPT>(codes + static_cast<size_t>(l) * D + col0, w);
     if (cg == 0) meta[l] = make_float2(s, z);
@@ -582,32 +572,61 @@ __device__ __forceinline__ void encode_row(const float* x, int r, int k_hi, int 
 
 // ------------------------------------------------------------- row decode
 
-// Loads and decodes one row slice (columns col0 .. col0 + CPT of tile row r)
-// into fp32: the high tier widened, the low tier as s * (c - z) (then the
-// inverse transform for the paper tiers with had). Lanes of a row take the
-// same branch (r is uniform across them).
+// The bytes of one row slice (columns col0 .. col0 + CPT of tile row r), so
+// that a kernel can have all its slices in flight before it decodes one. The
+// table formats (KIND >= kInt4) are loaded by decode_slice.
+template <int KIND, int CPT>
+struct RowSlice {
+  uint32_t w[KIND == kFp32 ? CPT : CPT / 2];
+  uint32_t m0, m1;
+};
+
 template <int KIND, int D, int CPT>
-__device__ __forceinline__ void decode_row(const uint8_t* tile, const uint8_t* codes,
-                                           const uint8_t* meta_bytes, int r, int k_hi, int cg,
-                                           int col0, bool had, float* x) {
-  if (KIND == kFp32) {
-    uint32_t w[CPT];
-    load_words<CPT * 4>(tile + (static_cast<size_t>(r) * D + col0) * 4, w);
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) x[j] = __uint_as_float(w[j]);
-    return;
-  }
-  if (r < k_hi) {
-    uint32_t w[CPT / 2];
-    load_words<CPT * 2>(tile + (static_cast<size_t>(r) * D + col0) * 2, w);
-#pragma unroll
-    for (int j = 0; j < CPT / 2; ++j) {
-      x[2 * j] = KIND >= kPaper ? f16_lo(w[j]) : bf16_lo(w[j]);
-      x[2 * j + 1] = KIND >= kPaper ? f16_hi(w[j]) : bf16_hi(w[j]);
+__device__ __forceinline__ RowSlice<KIND, CPT> load_row(const uint8_t* tile, const uint8_t* codes,
+                                                        const uint8_t* meta_bytes, int r, int k_hi,
+                                                        int col0) {
+  RowSlice<KIND, CPT> s;
+  if constexpr (KIND == kFp32) {
+    load_words<CPT * 4>(tile + (static_cast<size_t>(r) * D + col0) * 4, s.w);
+  } else if constexpr (KIND < kInt4) {
+    if (r < k_hi) {
+      load_words<CPT * 2>(tile + (static_cast<size_t>(r) * D + col0) * 2, s.w);
+    } else {
+      const size_t l = static_cast<size_t>(r - k_hi);
+      load_words<CPT>(codes + l * D + col0, s.w);
+      if constexpr (KIND == kPaper) {
+        s.m0 = reinterpret_cast<const uint32_t*>(meta_bytes)[l * (D / 32) + (col0 >> 5)];
+      } else {
+        const uint2 sz = reinterpret_cast<const uint2*>(meta_bytes)[l];
+        s.m0 = sz.x;
+        s.m1 = sz.y;
+      }
     }
-    return;
   }
-  if constexpr (KIND >= kInt4) {
+  return s;
+}
+
+// Decodes a slice into fp32: the high tier widened, the low tier as
+// s * (c - z) (then the inverse transform for the paper tiers with had).
+// Lanes of a row take the same branch (r is uniform across them).
+template <int KIND, int D, int CPT>
+__device__ __forceinline__ void decode_slice(const RowSlice<KIND, CPT>& sl, const uint8_t* tile,
+                                             const uint8_t* codes, const uint8_t* meta_bytes, int r,
+                                             int k_hi, int cg, int col0, bool had, float* x) {
+  if constexpr (KIND == kFp32) {
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) x[j] = __uint_as_float(sl.w[j]);
+  } else if constexpr (KIND >= kInt4) {
+    if (r < k_hi) {
+      uint32_t w[CPT / 2];
+      load_words<CPT * 2>(tile + (static_cast<size_t>(r) * D + col0) * 2, w);
+#pragma unroll
+      for (int j = 0; j < CPT / 2; ++j) {
+        x[2 * j] = f16_lo(w[j]);
+        x[2 * j + 1] = f16_hi(w[j]);
+      }
+      return;
+    }
     const size_t lr = static_cast<size_t>(r - k_hi);
     const float s_g = KIND == kNvfp4 ? load_global_scale<D>(meta_bytes, k_hi) : 1.0f;
     decode_slice_table<KIND, D>(codes + lr * code_row_bytes<KIND, D>(),
@@ -616,37 +635,41 @@ __device__ __forceinline__ void decode_row(const uint8_t* tile, const uint8_t* c
     if constexpr (KIND == kInt4) {
       if (had) fwht32_pair(reinterpret_cast<float(&)[16]>(*x), (cg & 1) != 0);
     }
-    return;
   } else {
-  const int l = r - k_hi;
-  uint32_t w[CPT / 4];
-  load_words<CPT>(codes + static_cast<size_t>(l) * D + col0, w);
-  float s, z;
-  if constexpr (KIND == kPaper) {
-    const uint32_t m =
-        reinterpret_cast<const uint32_t*>(meta_bytes)[static_cast<size_t>(l) * (D / 32) + (col0 >> 5)];
-    s = f16_lo(m);
-    z = f16_hi(m);
-  } else {
-    const float2 sz = reinterpret_cast<const float2*>(meta_bytes)[l];
-    s = sz.x;
-    z = sz.y;
-  }
-  // s * (c - z) as one FMA per value, with the transform's normalization
-  // folded into the factor
-  const float A = s * ((KIND == kPaper && had) ? kInvSqrt32 : 1.0f);
-  const float B0 = -A * z;
+    if (r < k_hi) {
 #pragma unroll
-  for (int j = 0; j < CPT / 4; ++j) {
-    x[4 * j + 0] = fmaf(A, ubyte<0>(w[j]), B0);
-    x[4 * j + 1] = fmaf(A, ubyte<1>(w[j]), B0);
-    x[4 * j + 2] = fmaf(A, ubyte<2>(w[j]), B0);
-    x[4 * j + 3] = fmaf(A, ubyte<3>(w[j]), B0);
+      for (int j = 0; j < CPT / 2; ++j) {
+        x[2 * j] = KIND >= kPaper ? f16_lo(sl.w[j]) : bf16_lo(sl.w[j]);
+        x[2 * j + 1] = KIND >= kPaper ? f16_hi(sl.w[j]) : bf16_hi(sl.w[j]);
+      }
+      return;
+    }
+    const float s = KIND == kPaper ? f16_lo(sl.m0) : __uint_as_float(sl.m0);
+    const float z = KIND == kPaper ? f16_hi(sl.m0) : __uint_as_float(sl.m1);
+    // s * (c - z) as one FMA per value, with the transform's normalization
+    // folded into the factor
+    const float A = s * ((KIND == kPaper && had) ? kInvSqrt32 : 1.0f);
+    const float B0 = -A * z;
+#pragma unroll
+    for (int j = 0; j < CPT / 4; ++j) {
+      x[4 * j + 0] = fmaf(A, ubyte<0>(sl.w[j]), B0);
+      x[4 * j + 1] = fmaf(A, ubyte<1>(sl.w[j]), B0);
+      x[4 * j + 2] = fmaf(A, ubyte<2>(sl.w[j]), B0);
+      x[4 * j + 3] = fmaf(A, ubyte<3>(sl.w[j]), B0);
+    }
+    if constexpr (KIND == kPaper && CPT == 16) {
+      if (had) fwht32_pair(reinterpret_cast<float(&)[16]>(*x), (cg & 1) != 0);
+    }
   }
-  if constexpr (KIND == kPaper && CPT == 16) {
-    if (had) fwht32_pair(reinterpret_cast<float(&)[16]>(*x), (cg & 1) != 0);
-  }
-  }
+}
+
+// Loads and decodes one row slice.
+template <int KIND, int D, int CPT>
+__device__ __forceinline__ void decode_row(const uint8_t* tile, const uint8_t* codes,
+                                           const uint8_t* meta_bytes, int r, int k_hi, int cg,
+                                           int col0, bool had, float* x) {
+  decode_slice<KIND, D, CPT>(load_row<KIND, D, CPT>(tile, codes, meta_bytes, r, k_hi, col0), tile,
+                             codes, meta_bytes, r, k_hi, cg, col0, had, x);
 }
 
 }  // namespace damp

@@ -1,0 +1,968 @@
+// Prefill at d = 128 on the matrix cores (App. A.5, prefill path; section 3.1
+// Eq. (1)): the recurrence of a chunk of C = 16 tokens in matrix form, with
+// fp32 accuracy.
+//
+// For tokens t = 0 .. C - 1 of a chunk with incoming state S0 and decays a_t,
+// let G_t = a_0 ... a_t and L_ts = a_{s+1} ... a_t. Eq. (1) unrolls to
+//   delta_t = v_t - G_t S0^T k_t - sum_{s<t} A_ts delta_s,  A_ts = L_ts beta_s k_t.k_s
+//   o_t     = G_t S0^T q_t + sum_{s<=t} B_ts delta_s,       B_ts = L_ts beta_s q_t.k_s
+//   S_C     = G_C S0 + sum_s k_s (L_{C-1,s} beta_s delta_s)^T
+// so with R = V - diag(G) K S0 and T = (I + A)^-1 (unit lower triangular,
+// by forward substitution):
+//   [U; O'] = [diag(E) T; B T] R,  E_s = L_{C-1,s} beta_s
+//   O = diag(G) Q S0 + O',  S_C = G_C S0 + K^T U.
+// T and B T do not depend on the state: they are formed for several chunks at
+// once, before the chunks run.
+//
+// Precision. Every fp32 operand x of a product enters the bf16 matrix cores
+// as x = hi + mid + lo, three bf16 numbers (exact: 24 bits), and products
+// accumulate in fp32. q and k are bf16 already, so K S0, Q S0, K K^T, Q K^T
+// and K^T U have one factor exact and take three products; a product of two
+// split factors takes the six whose weight is above 2^-26. Decay ratios are
+// running products as in the sequential form, never exponentials of sums.
+//
+// KDA's decay is per key channel, so k and q carry it: with the reference
+// token r = 7 of a chunk and rho_t the product of a channel's decays between
+// tokens r and t (1 at r),
+//   k~_t = k_t rho_t, q~_t = q_t rho_t, k^_s = k_s / rho_s
+// and, with S0' = diag(a_0 ... a_7) S0, the same formulas hold with L = G = 1:
+//   A_ts = beta_s k~_t.k^_s, S_C = diag(a_8 ... a_15) (S0' + K^^T U).
+// The eight-token products on either side of r must stay in [2^-96, 2^96];
+// a chunk where some channel leaves it (a zero decay included), or whose
+// inputs are not finite, runs token by token in fp32 (run_tokens).
+//
+// Mapping. A workgroup of four waves owns one (request, value head) tile;
+// wave w holds columns 32 w .. 32 w + 31 of the state for all 128 channels, in
+// natural channel order, as the accumulators of 32 x 32 matrix instructions
+// (64 registers a lane). The rows of an accumulator block are assigned so
+// that eight consecutive accumulator registers of a lane are eight consecutive
+// channels (or tokens): exactly the lane's part of the right-hand operand of
+// the next product, which is therefore split in registers, without any
+// exchange between lanes. The left-hand operands are read from LDS: rows of
+// k and q (16-byte pieces xor-swizzled by the row, so that the lanes of a
+// read hit distinct banks), and for K^T U the same rows through the
+// transposing LDS read. The stored tile passes through LDS once on the way in
+// and once on the way out, half its columns at a time, and takes its channel
+// permutation there, so that k, q and g are read as whole rows.
+//
+// What bounds it: the issue of vector instructions, about 800 per wave and
+// chunk besides 42 matrix instructions (GDN; KDA 1000 and 78), of which the
+// three-way splits are half. A wave alone issues one in 5 cycles, and a matrix
+// instruction keeps the SIMD's vector unit from others' use for about 22 of
+// its 32 cycles, so the kernel is held to 168 registers and 51 200 bytes of
+// LDS: three workgroups a CU. A register that spills costs more than it looks
+// (its reload waits for every load and store before it: 336 -> 440 us with
+// some ten in the loop), hence opaque() and the scheduling barriers. Chunks of
+// 16: the products within a chunk and T grow with its square.
+// Measured against the token-by-token fp32 kernel before it (two FMAs per
+// value and token for the read-outs, one for the update), GDN, B = 256, 32
+// heads, 64 tokens: 805 -> 320 us; KDA, B = 32, 250 tokens: 498 -> 270 us; GDN,
+// two requests of 1024 tokens: 728 -> 180 us; 2 tokens at B = 256: 154 -> 139 us
+// (GDN), 167 -> 164 us (KDA).
+#include <cfloat>
+#include <cstdint>
+
+#include "device.hpp"
+#include "internal.hpp"
+#include "prefill.hpp"
+
+namespace damp {
+namespace {
+
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+typedef float f4v __attribute__((ext_vector_type(4)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
+typedef short s4v __attribute__((ext_vector_type(4)));
+
+constexpr int kC = 16;    // tokens of a chunk
+constexpr int kD = 128;
+constexpr int kRow = 256;  // bytes of a row of 128 bf16
+constexpr int kPitch = 68;  // floats of a row of half the tile's columns in transit
+constexpr float kRhoMin = 0x1p-96f, kRhoMax = 0x1p96f;
+
+__device__ __forceinline__ f16v mfma32(u4v a, u4v b, f16v c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8v, a),
+                                                 __builtin_bit_cast(bf8v, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ f4v mfma16(u4v a, u4v b, f4v c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, a),
+                                                 __builtin_bit_cast(bf8v, b), c, 0, 0, 0);
+}
+
+// x = hi + mid + lo of two values, packed.
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t& hi, uint32_t& mid,
+                                       uint32_t& lo) {
+  hi = pack_bf16x2(x0, x1);
+  const float r0 = x0 - bf16_lo(hi), r1 = x1 - bf16_hi(hi);
+  mid = pack_bf16x2(r0, r1);
+  lo = pack_bf16x2(r0 - bf16_lo(mid), r1 - bf16_hi(mid));
+}
+
+// Hides how x was formed, so that the few instructions of an address are
+// repeated where it is used instead of every address of the token loop being
+// kept in registers.
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// The same by truncation, one vector cycle in ten less: for products whose
+// three parts all count (the rounded parts are smaller, so that the three
+// dropped products of two split factors are).
+__device__ __forceinline__ void split2_cut(float x0, float x1, uint32_t& hi, uint32_t& mid,
+                                           uint32_t& lo) {
+  constexpr uint32_t kTop = 0xffff0000u, kPair = 0x07060302u;  // the upper halves of two words
+  const float r0 = x0 - __uint_as_float(__float_as_uint(x0) & kTop);
+  const float r1 = x1 - __uint_as_float(__float_as_uint(x1) & kTop);
+  const float l0 = r0 - __uint_as_float(__float_as_uint(r0) & kTop);
+  const float l1 = r1 - __uint_as_float(__float_as_uint(r1) & kTop);
+  hi = __builtin_amdgcn_perm(__float_as_uint(x1), __float_as_uint(x0), kPair);
+  mid = __builtin_amdgcn_perm(__float_as_uint(r1), __float_as_uint(r0), kPair);
+  lo = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), kPair);
+}
+
+struct Split8 {
+  u4v part[3];  // hi, mid, lo of eight values
+};
+template <bool CUT = false>
+__device__ __forceinline__ Split8 split8(const float* x) {
+  Split8 s;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    uint32_t hi, mid, lo;
+    if (CUT) split2_cut(x[2 * j], x[2 * j + 1], hi, mid, lo);
+    else split2(x[2 * j], x[2 * j + 1], hi, mid, lo);
+    s.part[0][j] = hi;
+    s.part[1][j] = mid;
+    s.part[2][j] = lo;
+  }
+  return s;
+}
+
+// c + a b over split factors, smallest products first: three when a is exact
+// (NA = 1), the six above 2^-26 of the largest otherwise.
+template <int NA>
+__device__ __forceinline__ f16v mfma32_split(const u4v* a, const Split8& b, f16v c) {
+  if constexpr (NA == 1) {
+    c = mfma32(a[0], b.part[2], c);
+    c = mfma32(a[0], b.part[1], c);
+    return mfma32(a[0], b.part[0], c);
+  } else {
+    c = mfma32(a[2], b.part[0], c);
+    c = mfma32(a[0], b.part[2], c);
+    c = mfma32(a[1], b.part[1], c);
+    c = mfma32(a[1], b.part[0], c);
+    c = mfma32(a[0], b.part[1], c);
+    return mfma32(a[0], b.part[0], c);
+  }
+}
+
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// 16-byte piece ck of row r of a swizzled [rows][128] bf16 array.
+__device__ __forceinline__ int row_at(int r, int ck) { return r * kRow + ((ck ^ (r & 15)) << 4); }
+
+// Non-zero if a bf16 half of w is an infinity or a NaN.
+__device__ __forceinline__ uint32_t nonfinite(uint32_t w) {
+  return ((w & 0x7f807f80u) + 0x00800080u) & 0x80008000u;
+}
+
+// `n` rows of `bytes` bytes, `step` bytes apart, as a raw buffer that ends with
+// the last row: reads past it return zero and writes are dropped.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* base, int step, int bytes,
+                                                            int n) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (n - 1) * step + bytes,
+                                           0x00020000);
+}
+
+// LDS of one chunk's operands. GDN: kq holds the 16 rows of k, then of q, and
+// tm [U rows; O rows] as three bf16 parts. KDA: kq holds k~ and q~ in three
+// parts, kh k^ in three parts, tm the fp32 values (split when read).
+template <bool KDA>
+struct ChunkLds;
+template <>
+struct alignas(16) ChunkLds<false> {
+  uint8_t kq[1][32 * kRow];
+  uint16_t tm[3][32][kC];
+  float G[kC], a[kC], beta[kC];
+  int32_t flag;
+};
+template <>
+struct alignas(16) ChunkLds<true> {
+  uint8_t kq[3][32 * kRow];
+  uint8_t kh[3][16 * kRow];
+  float tm[32][kC];
+  float pre[kD], fin[kD];
+  float beta[kC];
+  int32_t flag[4], vflag[4];  // by staging wave; by wave, its columns of v
+};
+
+template <bool KDA>
+struct Prefill {
+  static constexpr int NC = KDA ? 1 : 4;  // chunks staged together
+  static constexpr int NA = KDA ? 3 : 1;
+  using Chunk = ChunkLds<KDA>;
+  static constexpr size_t kTransit = sizeof(float) * kD * kPitch;
+  static constexpr size_t kBytes =
+      NC * sizeof(Chunk) > kTransit ? NC * sizeof(Chunk) : kTransit;
+};
+static_assert(Prefill<true>::kBytes <= 54272 && Prefill<false>::kBytes <= 54272,
+              "three workgroups of a CU share 160 KB of LDS");
+
+// (I + A)^-1 by forward substitution, one column per lane (c = lane % 16, the
+// four lanes of a column alike), and the rows of [diag(E) T; B T] for a chunk
+// of n tokens (the rows of four tokens past the end are left out). ab: A rows
+// 0..15 and B rows 16..31, fp32, zero where s >= t (A) or s > t (B). On return
+// um[i] and om[i] hold rows 4 (lane / 16) + i of the two halves.
+__device__ __forceinline__ void solve_chunk(const float (*ab)[kC], int lane, int n,
+                                            const float (&e4)[4], float (&um)[4],
+                                            float (&om)[4]) {
+  const int c = opaque(lane & 15), quad = lane >> 4;
+  float T[kC];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) um[i] = om[i] = 0.0f;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) T[4 * g + i] = 0.0f;
+    if (4 * g < n) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int t = 4 * g + i;
+        float acc = t == c ? 1.0f : 0.0f;
+#pragma unroll
+        for (int s4 = 0; s4 < (t + 3) / 4; ++s4) {
+          const float4 a4 = *reinterpret_cast<const float4*>(&ab[t][4 * s4]);
+          const float av[4] = {a4.x, a4.y, a4.z, a4.w};
+#pragma unroll
+          for (int m = 0; m < 4; ++m)
+            if (4 * s4 + m < t) acc = fmaf(-av[m], T[4 * s4 + m], acc);
+        }
+        T[t] = acc;
+        um[i] = quad == g ? acc : um[i];  // the lane's own rows
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);  // four rows at a time: registers
+  }
+#pragma unroll
+  for (int s4 = 0; s4 < 4; ++s4) {
+    if (4 * s4 < n) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4 b4 = *reinterpret_cast<const float4*>(&ab[16 + 4 * quad + i][4 * s4]);
+        om[i] = fmaf(b4.x, T[4 * s4], om[i]);
+        om[i] = fmaf(b4.y, T[4 * s4 + 1], om[i]);
+        om[i] = fmaf(b4.z, T[4 * s4 + 2], om[i]);
+        om[i] = fmaf(b4.w, T[4 * s4 + 3], om[i]);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) um[i] *= e4[i];
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int KIND, bool KDA>
+__global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p) {
+  using P = Prefill<KDA>;
+  constexpr int NC = P::NC, NA = P::NA, CPT = 16, TPR = 8;
+  __shared__ __attribute__((aligned(16))) uint8_t lds_raw[P::kBytes];
+  typename P::Chunk* L = reinterpret_cast<typename P::Chunk*>(lds_raw);
+  float(*tbuf)[kPitch] = reinterpret_cast<float(*)[kPitch]>(lds_raw);
+
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int ph = lane >> 5, l32 = lane & 31;  // half: tokens (or channels) 8 ph ..
+  const int h = blockIdx.x, b = blockIdx.y;
+  const int T = p.T;
+  const int hk = h / (p.HV / p.HK);
+  const int col = 32 * wave + l32;  // this lane's state column
+  const size_t o_esize = p.o_bf16 ? 2 : 4;
+  const size_t o_step = static_cast<size_t>(p.HV) * kD * o_esize;
+  uint8_t* const o_col = static_cast<uint8_t*>(p.o) +
+                         ((static_cast<size_t>(b) * T * p.HV + h) * kD + col) * o_esize;
+  auto write_o = [&](int tok, float val) {
+    uint8_t* at = o_col + static_cast<size_t>(tok) * o_step;
+    if (p.o_bf16) *reinterpret_cast<uint16_t*>(at) = f32_to_bf16(val);
+    else *reinterpret_cast<float*>(at) = val;
+  };
+
+  const int slot = __builtin_amdgcn_readfirstlane(p.slot_idx[b]);
+  if (slot < 0 || slot >= p.num_slots) {  // padded request: o = 0, state untouched
+    if (p.o)
+      for (int tok = ph; tok < T; tok += 2) write_o(tok, 0.0f);
+    return;
+  }
+  uint8_t* tile = p.layer_base + static_cast<size_t>(slot) * p.slot_stride +
+                  static_cast<size_t>(h) * p.tile_stride;
+  const int k_hi = KIND == kFp32 ? kD : p.k_hi;
+  uint8_t* codes = tile + static_cast<size_t>(k_hi) * kD * 2;
+  uint8_t* meta_bytes = codes + static_cast<size_t>(kD - k_hi) * code_row_bytes<KIND, kD>();
+  const bool had = p.had != 0;
+
+  // rows of the inputs: token tok of this request and head
+  const size_t tok0 = static_cast<size_t>(b) * p.t_pitch + p.t0;
+  auto k_row = [&](int tok) { return ((tok0 + tok) * p.HK + hk) * kD; };
+  auto v_row = [&](int tok) { return (tok0 + tok) * p.HV + h; };
+
+  // ---- inputs of NC chunks, through buffer resources that end with the last
+  // token: later tokens read zeros
+  constexpr int NL = 4;
+  struct Ahead {
+    u4v k[KDA ? 1 : NL], q[KDA ? 1 : NL];
+    uint32_t kp[KDA ? NL : 1], qp[KDA ? NL : 1], gp[KDA ? NL : 1];
+    uint32_t v[KDA ? 8 : 1];
+    uint32_t g, beta;
+  } in;
+  const int kq_step = p.HK * kRow, v_step = p.HV * kRow;
+  auto load_inputs = [&](int tb0) {
+    const int lane = opaque(t) & 63, ph = lane >> 5, l32 = lane & 31, col = 32 * wave + l32;
+    const int ntok = T - tb0 < NC * kC ? T - tb0 : NC * kC;
+    const size_t row = tok0 + tb0;
+    const auto rk = rows_rsrc(p.k + (row * p.HK + hk) * kD, kq_step, kRow, ntok);
+    const auto rq = rows_rsrc(p.q + (row * p.HK + hk) * kD, kq_step, kRow, ntok);
+    const auto rb = rows_rsrc(p.beta + row * p.HV + h, 2 * p.HV, 2, ntok);
+    if constexpr (!KDA) {  // wave w: chunk w; 16 bytes of four rows per load
+      const auto rg = rows_rsrc(p.g + row * p.HV + h, 2 * p.HV, 2, ntok);
+      const int tt = opaque(kC * wave + (lane >> 4));
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        const int kq = (tt + 4 * i) * kq_step + 16 * (lane & 15);
+        in.k[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, kq, 0, 0);
+        in.q[i] = __builtin_amdgcn_raw_buffer_load_b128(rq, kq, 0, 0);
+      }
+      const int ts = (kC * wave + (lane & 15)) * 2 * p.HV;
+      in.g = __builtin_amdgcn_raw_buffer_load_b16(rg, ts, 0, 0);
+      in.beta = __builtin_amdgcn_raw_buffer_load_b16(rb, ts, 0, 0);
+    } else {  // wave w: tokens 8 (w / 2) + 4 (lane / 32) .. + 3, two channels per lane
+      const auto rg = rows_rsrc(p.g + (row * p.HV + h) * kD, v_step, kRow, ntok);
+      const auto rv = rows_rsrc(p.v + (row * p.HV + h) * kD, v_step, kRow, ntok);
+      const int tt = 8 * (wave >> 1) + 4 * ph, at = 128 * (wave & 1) + 4 * l32;
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        const int kq = (tt + i) * kq_step + at, gv = (tt + i) * v_step + at;
+        in.kp[i] = __builtin_amdgcn_raw_buffer_load_b32(rk, kq, 0, 0);
+        in.qp[i] = __builtin_amdgcn_raw_buffer_load_b32(rq, kq, 0, 0);
+        in.gp[i] = __builtin_amdgcn_raw_buffer_load_b32(rg, gv, 0, 0);
+      }
+      in.beta = __builtin_amdgcn_raw_buffer_load_b16(rb, (lane & 15) * 2 * p.HV, 0, 0);
+      const int v_at = 8 * ph * v_step + 2 * col;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        in.v[KDA ? e : 0] = __builtin_amdgcn_raw_buffer_load_b16(rv, e * v_step + v_at, 0, 0);
+    }
+  };
+  // one load per 128-byte line of the rows of the NC chunks from token tb0, so
+  // that load_inputs finds them in the L2; the caller drops the values
+  auto touch = [&](int tb0, uint32_t& x0, uint32_t& x1) {
+    const int t = opaque(threadIdx.x);
+    const int ntok = T - tb0 < NC * kC ? T - tb0 : NC * kC;
+    const size_t row = tok0 + tb0;
+    const auto rk = rows_rsrc(p.k + (row * p.HK + hk) * kD, kq_step, kRow, ntok);
+    const auto rq = rows_rsrc(p.q + (row * p.HK + hk) * kD, kq_step, kRow, ntok);
+    const auto rv = rows_rsrc(p.v + (row * p.HV + h) * kD, v_step, kRow, ntok);
+    if constexpr (!KDA) {
+      const int tt = (t >> 1) & 63, line = 128 * (t & 1);
+      x0 = t < 128 ? __builtin_amdgcn_raw_buffer_load_b32(rk, tt * kq_step + line, 0, 0)
+                   : __builtin_amdgcn_raw_buffer_load_b32(rq, tt * kq_step + line, 0, 0);
+      x1 = t < 128 ? __builtin_amdgcn_raw_buffer_load_b32(rv, tt * v_step + line, 0, 0) : 0u;
+    } else {
+      const auto rg = rows_rsrc(p.g + (row * p.HV + h) * kD, v_step, kRow, ntok);
+      const int tt = (t >> 1) & 15, line = 128 * (t & 1);
+      x0 = wave == 0   ? __builtin_amdgcn_raw_buffer_load_b32(rk, tt * kq_step + line, 0, 0)
+           : wave == 1 ? __builtin_amdgcn_raw_buffer_load_b32(rq, tt * kq_step + line, 0, 0)
+           : wave == 2 ? __builtin_amdgcn_raw_buffer_load_b32(rv, tt * v_step + line, 0, 0)
+                       : __builtin_amdgcn_raw_buffer_load_b32(rg, tt * v_step + line, 0, 0);
+      x1 = 0u;
+    }
+  };
+
+  uint32_t seen0, seen1;
+  touch(0, seen0, seen1);
+
+  // ---- the tile, row slices through LDS into natural channel order: thread
+  // t moves columns 16 cg .. + 15 of tile rows t / 8 + 32 i
+  const int cg = t & 7, col0 = cg * CPT, rr = t >> 3;
+  int u_of[4];
+  f16v S[4];
+  {
+    RowSlice<KIND, CPT> raw[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      raw[i] = load_row<KIND, kD, CPT>(tile, codes, meta_bytes, rr + 32 * i, k_hi, col0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = rr + 32 * i;
+      u_of[i] = p.perm ? (static_cast<int>(p.perm[static_cast<size_t>(h) * kD + r]) & (kD - 1)) : r;
+    }
+    float x[4][CPT];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      decode_slice<KIND, kD, CPT>(raw[i], tile, codes, meta_bytes, rr + 32 * i, k_hi, cg, col0, had,
+                                  x[i]);
+    // half the columns at a time: those of waves 2 hf and 2 hf + 1
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      if ((cg >> 2) == hf) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int q4 = 0; q4 < CPT / 4; ++q4)
+            *reinterpret_cast<float4*>(&tbuf[u_of[i]][(col0 & 63) + 4 * q4]) =
+                make_float4(x[i][4 * q4], x[i][4 * q4 + 1], x[i][4 * q4 + 2], x[i][4 * q4 + 3]);
+      }
+      __syncthreads();
+      // accumulator register 8 cc + e of block bb: channel 32 bb + 16 cc + 8 ph + e
+      if ((wave >> 1) == hf) {
+#pragma unroll
+        for (int bb = 0; bb < 4; ++bb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            S[bb][i] = tbuf[32 * bb + 16 * (i >> 3) + 8 * ph + (i & 7)][col & 63];
+      }
+      __syncthreads();
+    }
+  }
+
+  // the lane id, formed anew in each phase (see opaque)
+  auto lane_now = [&]() { return opaque(t) & 63; };
+
+  // ---- one flagged chunk token by token in fp32 (n tokens from token tb):
+  // rows of k and q in bf16 from LDS; KDA's decays in fp32 from LDS
+  auto run_tokens = [&](const typename P::Chunk& ck, int tb, int n) {
+    const uint8_t* kq = ck.kq[0];
+    const int lane = lane_now(), ph = lane >> 5, col = 32 * wave + (lane & 31);
+#pragma unroll 1
+    for (int tok = 0; tok < n; ++tok) {
+      float w = 0.0f, pq = 0.0f, qk = 0.0f;
+      const int at = opaque(row_at(tok, ph));  // of k; q 16 rows on
+#pragma unroll
+      for (int bb = 0; bb < 4; ++bb)
+#pragma unroll
+        for (int cc = 0; cc < 2; ++cc) {
+          const int piece = 4 * bb + 2 * cc + ph;
+          const uint8_t* row = kq + (at ^ ((4 * bb + 2 * cc) << 4));
+          const u4v k8 = *reinterpret_cast<const u4v*>(row);
+          const u4v q8 = *reinterpret_cast<const u4v*>(row + 16 * kRow);
+          float a8[8];
+          if constexpr (KDA) {
+            const float* ar = reinterpret_cast<const float*>(ck.kq[NA > 1 ? 1 : 0]) + tok * kD + 8 * piece;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a8[e] = ar[e];
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a8[e] = ck.a[tok];
+          }
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float kf = e & 1 ? bf16_hi(k8[e >> 1]) : bf16_lo(k8[e >> 1]);
+            const float qf = e & 1 ? bf16_hi(q8[e >> 1]) : bf16_lo(q8[e >> 1]);
+            const float x = S[bb][8 * cc + e] * a8[e];
+            S[bb][8 * cc + e] = x;
+            w = fmaf(kf, x, w);
+            pq = fmaf(qf, x, pq);
+            qk = fmaf(qf, kf, qk);
+          }
+        }
+      w += __shfl_xor(w, 32, 64);
+      pq += __shfl_xor(pq, 32, 64);
+      qk += __shfl_xor(qk, 32, 64);
+      const float vf = bf16_to_f32(p.v[v_row(tb + tok) * kD + col]);
+      const float beta = ck.beta[tok], delta = vf - w;
+      if (p.o && ph == 0) write_o(tb + tok, p.scale * fmaf(beta * qk, delta, pq));
+      const float bd = beta * delta;
+#pragma unroll
+      for (int bb = 0; bb < 4; ++bb)
+#pragma unroll
+        for (int cc = 0; cc < 2; ++cc) {
+          const u4v k8 = *reinterpret_cast<const u4v*>(kq + (at ^ ((4 * bb + 2 * cc) << 4)));
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float kf = e & 1 ? bf16_hi(k8[e >> 1]) : bf16_lo(k8[e >> 1]);
+            S[bb][8 * cc + e] = fmaf(kf, bd, S[bb][8 * cc + e]);
+          }
+        }
+    }
+  };
+
+
+  auto chunk_flag = [&](int c) -> bool {
+    if constexpr (KDA)
+      return (L[c].flag[0] | L[c].flag[1] | L[c].flag[2] | L[c].flag[3] | L[c].vflag[0] |
+              L[c].vflag[1] | L[c].vflag[2] | L[c].vflag[3]) != 0;
+    else
+      return L[c].flag != 0;
+  };
+
+  // ---- GDN staging, wave-local: wave w stages chunk w
+  auto stage_gdn = [&](int tb) {
+    if constexpr (!KDA) {
+      if (tb >= T) return;
+      typename P::Chunk& ck = L[wave];
+      const int lane = lane_now();
+      uint32_t bad = 0u;
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        const int row = (lane >> 4) + 4 * i;
+        *reinterpret_cast<u4v*>(ck.kq[0] + row_at(row, lane & 15)) = in.k[i];
+        *reinterpret_cast<u4v*>(ck.kq[0] + row_at(16 + row, lane & 15)) = in.q[i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          bad |= nonfinite(in.k[i][j]) | nonfinite(in.q[i][j]);
+      }
+      const float a = __expf(bf16_to_f32(static_cast<uint16_t>(in.g)));  // 1 past the end
+      const float beta = bf16_to_f32(static_cast<uint16_t>(in.beta));
+      if (!(a <= FLT_MAX) || !(fabsf(beta) <= FLT_MAX)) bad = 1u;
+      const bool flagged = __builtin_amdgcn_ballot_w64(bad != 0u) != 0;
+      if (lane == 0) ck.flag = flagged ? 1 : 0;
+      if (lane < kC) {
+        ck.a[lane] = a;
+        ck.beta[lane] = beta;
+      }
+      if (flagged) return;
+      // decay ratios: this lane's column s, rows t = 4 quad + i
+      const int s = lane & 15, quad = lane >> 4;
+      float Lr[4] = {0.0f, 0.0f, 0.0f, 0.0f}, G = 1.0f, run = 1.0f, Gs = 1.0f;
+#pragma unroll
+      for (int tt = 0; tt < kC; ++tt) {
+        const float at = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), tt));
+        G *= at;
+        if (s == tt) Gs = G;
+        run = tt <= s ? 1.0f : run * at;
+        if (quad == (tt >> 2)) Lr[tt & 3] = run;
+      }
+      if (lane < kC) ck.G[lane] = Gs;
+      const float E = run * beta;  // L_{15,s} beta_s
+      wave_sync();
+      f4v kk = {0.0f, 0.0f, 0.0f, 0.0f}, qk = kk;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const u4v fk = *reinterpret_cast<const u4v*>(ck.kq[0] + row_at(s, 4 * ks + quad));
+        const u4v fq = *reinterpret_cast<const u4v*>(ck.kq[0] + row_at(16 + s, 4 * ks + quad));
+        kk = mfma16(fk, fk, kk);
+        qk = mfma16(fq, fk, qk);
+      }
+      float(*ab)[kC] = reinterpret_cast<float(*)[kC]>(ck.tm);
+      float e4[4], um[4], om[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int tt = 4 * quad + i;
+        const float f = Lr[i] * beta;
+        ab[tt][s] = s < tt ? f * kk[i] : 0.0f;
+        ab[16 + tt][s] = s <= tt ? f * qk[i] : 0.0f;
+        e4[i] = __shfl(E, tt, 64);
+      }
+      wave_sync();
+      solve_chunk(ab, lane, T - tb, e4, um, om);
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        uint32_t hi, mid, lo;
+        split2(um[i], om[i], hi, mid, lo);
+        const int tt = 4 * quad + i;
+        ck.tm[0][tt][s] = static_cast<uint16_t>(hi);
+        ck.tm[1][tt][s] = static_cast<uint16_t>(mid);
+        ck.tm[2][tt][s] = static_cast<uint16_t>(lo);
+        ck.tm[0][16 + tt][s] = static_cast<uint16_t>(hi >> 16);
+        ck.tm[1][16 + tt][s] = static_cast<uint16_t>(mid >> 16);
+        ck.tm[2][16 + tt][s] = static_cast<uint16_t>(lo >> 16);
+      }
+    }
+  };
+
+  // ---- KDA staging by the whole workgroup: waves 0 and 1 take the first
+  // eight tokens, waves 2 and 3 the others
+  auto stage_kda = [&](int tb, int who) {
+    if constexpr (KDA) {
+      const int half = wave >> 1;
+      const int lane = lane_now(), ph = lane >> 5, l32 = lane & 31;
+      typename P::Chunk& ck = L[0];
+      // cum[i]: the channel's product between token 7 and token i of the lane's four
+      float a[2][4], cum[2][4];
+      uint32_t bad = 0u;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        a[0][i] = __expf(bf16_lo(in.gp[i]));
+        a[1][i] = __expf(bf16_hi(in.gp[i]));
+        bad |= nonfinite(in.kp[i]) | nonfinite(in.qp[i]);
+      }
+      float whole[2];
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        const float mine = (a[m][0] * a[m][1]) * (a[m][2] * a[m][3]);
+        const float other = __shfl_xor(mine, 32, 64);
+        float run = (half == 0) == (ph == 0) ? other : 1.0f;  // the four tokens nearer to token 7
+        if (half == 0) {
+#pragma unroll
+          for (int i = 3; i >= 0; --i) {
+            cum[m][i] = run;
+            run *= a[m][i];
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            run *= a[m][i];
+            cum[m][i] = run;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (!(cum[m][i] >= kRhoMin && cum[m][i] <= kRhoMax)) bad = 1u;
+        whole[m] = run;
+        if (!(run <= FLT_MAX)) bad = 1u;
+      }
+      const float beta = bf16_to_f32(static_cast<uint16_t>(in.beta));
+      if (!(fabsf(beta) <= FLT_MAX)) bad = 1u;
+      const bool flagged = __builtin_amdgcn_ballot_w64(bad != 0u) != 0;
+      if (lane == 0) ck.flag[wave] = flagged ? 1 : 0;
+      uint32_t vbad = 0u;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) vbad |= nonfinite(in.v[KDA ? e : 0]);
+      const bool v_flagged = __builtin_amdgcn_ballot_w64(vbad != 0u) != 0;
+      if (lane == 0) ck.vflag[wave] = v_flagged ? 1 : 0;
+      if (wave == 0 && lane < kC) ck.beta[lane] = beta;
+      // the lanes of a channel's far tokens hold the product of all eight
+      if ((half == 0) == (ph == 0))
+        *reinterpret_cast<float2*>(&(half == 0 ? ck.pre : ck.fin)[64 * (wave & 1) + 2 * l32]) =
+            make_float2(whole[0], whole[1]);
+      // row 8 half + 4 ph + i: (at ^ 16 i) + i rows; q 16 rows after k
+      const int first = 8 * half + 4 * ph;
+      const int at = row_at(first, 8 * (wave & 1) + (l32 >> 2)) + 4 * (l32 & 3);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = (at ^ (i << 4)) + i * kRow;
+        const float i0 = refined_rcp(cum[0][i]), i1 = refined_rcp(cum[1][i]);
+        const float f0 = half == 0 ? i0 : cum[0][i], f1 = half == 0 ? i1 : cum[1][i];
+        const float n0 = half == 0 ? cum[0][i] : i0, n1 = half == 0 ? cum[1][i] : i1;
+        const float k0 = bf16_lo(in.kp[i]), k1 = bf16_hi(in.kp[i]);
+        uint32_t s3[3];
+        split2(k0 * f0, k1 * f1, s3[0], s3[1], s3[2]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+          *reinterpret_cast<uint32_t*>(ck.kq[KDA ? j : 0] + row) = s3[j];
+        split2(bf16_lo(in.qp[i]) * f0, bf16_hi(in.qp[i]) * f1, s3[0], s3[1], s3[2]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+          *reinterpret_cast<uint32_t*>(ck.kq[KDA ? j : 0] + row + 16 * kRow) = s3[j];
+        split2(k0 * n0, k1 * n1, s3[0], s3[1], s3[2]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) *reinterpret_cast<uint32_t*>(ck.kh[j] + row) = s3[j];
+      }
+      __syncthreads();
+      const bool slow = __builtin_amdgcn_readfirstlane(chunk_flag(0) ? 1 : 0) != 0;
+      if (__builtin_expect(slow, 0)) {  // k, q and the decays themselves instead
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uint8_t* row = ck.kq[0] + (at ^ (i << 4)) + i * kRow;
+          *reinterpret_cast<uint32_t*>(row) = in.kp[i];
+          *reinterpret_cast<uint32_t*>(row + 16 * kRow) = in.qp[i];
+          reinterpret_cast<float2*>(ck.kq[NA > 1 ? 1 : 0])[(first + i) * (kD / 2) + 32 * (wave & 1) +
+                                                           l32] = make_float2(a[0][i], a[1][i]);
+        }
+        __syncthreads();
+        return;
+      }
+      // one wave of each half of the rows: A = beta_s k~_t.k^_s, B = beta_s q~_t.k^_s
+      const int s = lane & 15, quad = lane >> 4, rows = (wave ^ who) & 1;
+      if (((wave ^ who) & 2) == 0) {
+        f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        const int at_b = opaque(row_at(s, quad)), at_a = at_b + 16 * rows * kRow;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          u4v fa[3], fb[3];
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            fa[j] = *reinterpret_cast<const u4v*>(ck.kq[KDA ? j : 0] + (at_a ^ (ks << 6)));
+            fb[j] = *reinterpret_cast<const u4v*>(ck.kh[j] + (at_b ^ (ks << 6)));
+          }
+          acc = mfma16(fa[2], fb[0], acc);
+          acc = mfma16(fa[0], fb[2], acc);
+          acc = mfma16(fa[1], fb[1], acc);
+          acc = mfma16(fa[1], fb[0], acc);
+          acc = mfma16(fa[0], fb[1], acc);
+          acc = mfma16(fa[0], fb[0], acc);
+        }
+        const float bs = ck.beta[s];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int tt = 4 * quad + i;
+          const bool in_tri = rows == 0 ? s < tt : s <= tt;
+          ck.tm[16 * rows + tt][s] = in_tri ? bs * acc[i] : 0.0f;
+        }
+      }
+      __syncthreads();
+      if (wave == who) {  // the others start on the chunk; they meet where it needs tm
+        float e4[4], um[4], om[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e4[i] = ck.beta[4 * quad + i];
+        solve_chunk(ck.tm, lane, T - tb, e4, um, om);
+        wave_sync();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          ck.tm[4 * quad + i][s] = um[i];
+          ck.tm[16 + 4 * quad + i][s] = om[i];
+        }
+      }
+    }
+  };
+
+  // ---- one chunk of up to 16 tokens from token tb on this wave's columns
+  // (vr: v of tokens 8 ph + e, this lane's column); false, and nothing done, if
+  // that v is not finite (GDN; KDA's flags have it)
+  auto run_chunk = [&](const typename P::Chunk& ck, int tb, const uint32_t (&vr)[8]) -> bool {
+    const int lane = lane_now(), ph = lane >> 5, l32 = lane & 31, col = 32 * wave + l32;
+    // rows of the left-hand operands: lane l32 is row m of the 32; m % 16 bits
+    // (r, p, i) stand for token (p, r, i), so that a lane's accumulators 0..7
+    // (8..15) are tokens 8 ph .. 8 ph + 7 of the first (second) 16 rows
+    const int m_tok = 8 * ((l32 >> 2) & 1) + 4 * ((l32 >> 3) & 1) + (l32 & 3);
+    const int m_row = (l32 & 16) + m_tok;
+    // transposing read of K^T: lane l32 of half ph asks for row s = 8 ph + 4 x + (l32 % 16) / 4,
+    // channels 32 bb + 16 (l32 / 16) + 8 p' + 4 r0 with l32 % 4 = 2 r0 + p'
+    const int tr_s = 8 * ph + ((l32 >> 2) & 3);
+    const int tr_ck = 2 * (l32 >> 4) + (l32 & 1), tr_half = ((l32 >> 1) & 1) * 8;
+    if constexpr (KDA) {
+#pragma unroll
+      for (int bb = 0; bb < 4; ++bb)
+#pragma unroll
+        for (int c2 = 0; c2 < 4; ++c2) {
+          const float4 f = *reinterpret_cast<const float4*>(
+              &ck.pre[32 * bb + 16 * (c2 >> 1) + 8 * ph + 4 * (c2 & 1)]);
+          S[bb][4 * c2] *= f.x;
+          S[bb][4 * c2 + 1] *= f.y;
+          S[bb][4 * c2 + 2] *= f.z;
+          S[bb][4 * c2 + 3] *= f.w;
+        }
+    }
+    // [K; Q] S0: accumulators 0..7 are rows k_t, 8..15 rows q_t, t = 8 ph + e
+    f16v acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+    const int a_at = row_at(m_row, ph);  // piece 2 ks + ph: bits 5 and up xor 2 ks
+    Split8 sb;
+    u4v fa[NA];
+    auto step_operands = [&](int ks) {
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = S[ks >> 1][8 * (ks & 1) + e];
+      sb = split8<!KDA>(x);
+#pragma unroll
+      for (int j = 0; j < NA; ++j)
+        fa[j] = *reinterpret_cast<const u4v*>(ck.kq[j] + (a_at ^ (ks << 5)));
+    };
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      step_operands(ks);
+      acc = mfma32_split<NA>(fa, sb, acc);
+      if (KDA) __builtin_amdgcn_sched_barrier(0);  // one step's operands at a time: registers
+    }
+    if constexpr (KDA) __syncthreads();  // tm is there
+    // R = V - G K S0, and the start G Q S0 of O
+    float R[8];
+    if constexpr (KDA) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        R[e] = bf16_lo(vr[e]) - acc[e];
+        acc[e] = 0.0f;
+      }
+    } else {
+      uint32_t bad = 0u;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) bad |= nonfinite(vr[e]);
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad != 0u) != 0, 0)) return false;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float G = ck.G[8 * ph + e];
+        R[e] = fmaf(-G, acc[e], bf16_lo(vr[e]));
+        acc[e] = 0.0f;
+        acc[8 + e] *= G;
+      }
+    }
+    {
+      const Split8 sr = split8(R);
+      Split8 tm;
+      if constexpr (KDA) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = ck.tm[m_row][8 * ph + e];
+        tm = split8(x);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+          tm.part[j] = *reinterpret_cast<const u4v*>(&ck.tm[j][m_row][8 * ph]);
+      }
+      acc = mfma32_split<3>(tm.part, sr, acc);
+    }
+    if (p.o) {
+      const int o_row = kD * static_cast<int>(o_esize), step = p.HV * o_row;
+      const auto ro = rows_rsrc(static_cast<uint8_t*>(p.o) +
+                                    ((static_cast<size_t>(b) * T + tb) * p.HV + h) * o_row,
+                                step, o_row, T - tb < kC ? T - tb : kC);
+      const int at = 8 * ph * step + col * static_cast<int>(o_esize);
+      if (p.o_bf16) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(p.scale * acc[8 + e]), ro, at + e * step,
+                                                0, 0);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(p.scale * acc[8 + e]), ro,
+                                                at + e * step, 0, 0);
+      }
+    }
+    // S = G_C S0 + K^T U
+    float U[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) U[e] = acc[e];
+    const Split8 su = split8<!KDA>(U);
+    float gc = 1.0f;
+    if constexpr (!KDA) gc = ck.G[kC - 1];
+    typedef __attribute__((address_space(3))) s4v* lds_s4;
+    const int tr_at0 = row_at(tr_s, tr_ck) + tr_half, tr_at1 = row_at(tr_s + 4, tr_ck) + tr_half;
+#pragma unroll
+    for (int bb = 0; bb < 4; ++bb) {
+      if constexpr (!KDA) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) S[bb][i] *= gc;
+      }
+      u4v fa[NA];
+#pragma unroll
+      for (int j = 0; j < NA; ++j) {
+        const uint8_t* rows;
+        if constexpr (KDA) rows = ck.kh[j];
+        else rows = ck.kq[0];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          const s4v v4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (lds_s4)(rows + ((x ? tr_at1 : tr_at0) ^ (bb << 6))));
+          const uint2 w2 = __builtin_bit_cast(uint2, v4);
+          fa[j][2 * x] = w2.x;
+          fa[j][2 * x + 1] = w2.y;
+        }
+      }
+      S[bb] = mfma32_split<NA>(fa, su, S[bb]);
+    }
+    if constexpr (KDA) {
+#pragma unroll
+      for (int bb = 0; bb < 4; ++bb)
+#pragma unroll
+        for (int c2 = 0; c2 < 4; ++c2) {
+          const float4 f = *reinterpret_cast<const float4*>(
+              &ck.fin[32 * bb + 16 * (c2 >> 1) + 8 * ph + 4 * (c2 & 1)]);
+          S[bb][4 * c2] *= f.x;
+          S[bb][4 * c2 + 1] *= f.y;
+          S[bb][4 * c2 + 2] *= f.z;
+          S[bb][4 * c2 + 3] *= f.w;
+        }
+    }
+    return true;
+  };
+
+  auto load_v = [&](int tb, uint32_t (&vr)[8]) {
+    const auto rv = rows_rsrc(p.v + ((tok0 + tb) * p.HV + h) * kD, v_step, kRow,
+                              T - tb < kC ? T - tb : kC);
+    const int lane = lane_now(), v_at = 8 * (lane >> 5) * v_step + 2 * (32 * wave + (lane & 31));
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      vr[e] = __builtin_amdgcn_raw_buffer_load_b16(rv, e * v_step + v_at, 0, 0);
+  };
+#pragma unroll 1
+  for (int tb0 = 0; tb0 < T; tb0 += NC * kC) {
+    asm volatile("" ::"v"(seen0), "v"(seen1));
+    load_inputs(tb0);
+    uint32_t vr[8];
+    if constexpr (KDA) {
+      stage_kda(tb0, (tb0 / kC + h) & 3);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) vr[e] = in.v[KDA ? e : 0];
+    } else {
+      stage_gdn(tb0 + kC * wave);
+      __syncthreads();
+    }
+    if (tb0 + NC * kC < T) touch(tb0 + NC * kC, seen0, seen1);
+#pragma unroll 1
+    for (int c = 0; c < NC && tb0 + kC * c < T; ++c) {
+      const int tb = tb0 + kC * c;
+      bool slow = chunk_flag(c);
+      if constexpr (!KDA) load_v(tb, vr);
+      if (!__builtin_amdgcn_readfirstlane(slow ? 1 : 0)) slow = !run_chunk(L[c], tb, vr);
+      if (__builtin_expect(__builtin_amdgcn_readfirstlane(slow ? 1 : 0), 0))
+        run_tokens(L[c], tb, T - tb < kC ? T - tb : kC);
+    }
+    __syncthreads();
+  }
+
+  // ---- store the final state per its tier, as it came
+  const int rs = opaque(rr), cs = opaque(cg), ps = opaque(ph);
+  float x[4][CPT];
+#pragma unroll
+  for (int hf = 0; hf < 2; ++hf) {
+    if ((wave >> 1) == hf) {
+#pragma unroll
+      for (int bb = 0; bb < 4; ++bb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          tbuf[32 * bb + 16 * (i >> 3) + 8 * ps + (i & 7)][col & 63] = S[bb][i];
+    }
+    __syncthreads();
+    if ((cs >> 2) == hf) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q4 = 0; q4 < CPT / 4; ++q4) {
+          const float4 v4 =
+              *reinterpret_cast<const float4*>(&tbuf[u_of[i]][16 * (cs & 3) + 4 * q4]);
+          x[i][4 * q4] = v4.x;
+          x[i][4 * q4 + 1] = v4.y;
+          x[i][4 * q4 + 2] = v4.z;
+          x[i][4 * q4 + 3] = v4.w;
+        }
+    }
+    __syncthreads();
+  }
+  float s_g = 1.0f;
+  if constexpr (KIND == kNvfp4) {  // the global scale of the final low tier
+    float amax = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (rs + 32 * i >= k_hi)
+#pragma unroll
+        for (int j = 0; j < CPT; ++j) amax = fmaxf(amax, fabsf(x[i][j]));
+    s_g = nvfp4_global(block_max<256>(amax));
+    if (t == 0) store_global_scale<kD>(meta_bytes, k_hi, s_g);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    encode_row<KIND, kD, CPT, TPR>(x[i], rs + 32 * i, k_hi, cs, 16 * cs, tile, codes, meta_bytes, had,
+                                   s_g);
+}
+
+template <int KIND>
+void launch_kind(bool kda, const PrefillParams& p, int B, hipStream_t stream) {
+  const dim3 grid(p.HV, B), block(256);
+  if (kda)
+    hipLaunchKernelGGL((prefill_chunk128<KIND, true>), grid, block, 0, stream, p);
+  else
+    hipLaunchKernelGGL((prefill_chunk128<KIND, false>), grid, block, 0, stream, p);
+}
+
+}  // namespace
+
+void launch_prefill_chunk128(int codec, bool kda, const PrefillParams& p, int B,
+                             hipStream_t stream) {
+  switch (codec) {
+    case kCodecFp32: launch_kind<kFp32>(kda, p, B, stream); break;
+    case kCodecPaper: launch_kind<kPaper>(kda, p, B, stream); break;
+    case kCodecInt4: launch_kind<kInt4>(kda, p, B, stream); break;
+    case kCodecFp8: launch_kind<kFp8>(kda, p, B, stream); break;
+    case kCodecNvfp4: launch_kind<kNvfp4>(kda, p, B, stream); break;
+    default: launch_kind<kMixed>(kda, p, B, stream); break;
+  }
+}
+
+}  // namespace damp

@@ -188,3 +188,87 @@ def test_calibrate_sequence_gdn_vanishing_decay():
     assert np.isfinite(sums).all()
     np.testing.assert_allclose(sums[0], cal_ref.sums[0, 0], rtol=2e-3)
     np.testing.assert_allclose(sums[1], cal_ref.sums[0, 1], rtol=1e-5)
+
+
+@pytest.mark.parametrize("kda", [False, True])
+@pytest.mark.parametrize("T", [1, 4, 5, 15, 16, 17, 33, 64, 65, 130])
+def test_prefill_chunk_edges(kda, T):
+    """d = 128 runs in chunks of 16 tokens, several staged together: one token,
+    the edges of the four-row groups, of a chunk and of a staging block, and a
+    partial last chunk. FP32 state, so o and the state carry fp32 rounding
+    only (the bar of the FP32 path)."""
+    d, HK, HV, B = 128, 2 if kda else 1, 2, 2
+    seed = 760 + T
+    slots = inputs.slot_order(seed, B + 1, B)
+    perm = inputs.random_perms(seed, HV, d)
+    ref = orc.Pool(orc.KIND_FP32, d, d, 0, 1, B + 1, HV)
+    orc.pack(ref, 0, slots, inputs.synthetic_states(seed, B, HV, d), perm)
+    gpool = gpu_pool_from(ref, D)
+    inp = inputs.as_prefill(inputs.decode_inputs(seed, T, B, HK, HV, d, kda=kda))
+    o_gpu, o_ref = _run(kda, ref, gpool, slots, inp, perm)
+    state = gpool.buffer.cpu().numpy().view(np.float32)
+    err, s_err = rel_l2(o_gpu, o_ref), rel_l2(state, ref.buf.view(np.float32))
+    _say(f"  T={T} kda={kda} o rel-L2 {err:.2e} state rel-L2 {s_err:.2e}")
+    assert err <= 1e-5 and s_err <= 1e-5
+
+
+@pytest.mark.parametrize("kda", [False, True])
+def test_prefill_inputs_at_odd_addresses(kda):
+    """q, k, v (16 bytes) and KDA's g (4 bytes) at addresses the d = 128 kernel
+    does not take go through the generic kernel: the same outputs and state to
+    fp32 rounding."""
+    d, HK, HV, B, T = 128, 2, 2, 2, 21
+    seed = 790
+    ref = orc.Pool(orc.KIND_FP32, d, d, 0, 1, B, HV)
+    orc.pack(ref, 0, np.arange(B), inputs.synthetic_states(seed, B, HV, d))
+    inp = dev_inputs(inputs.as_prefill(inputs.decode_inputs(seed, T, B, HK, HV, d, kda=kda)))
+    fn = D.damp_state_prefill_kda if kda else D.damp_state_prefill_gdn
+
+    def shifted(t):  # the same values, 2 bytes off
+        raw = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")
+        raw[1:] = t.reshape(-1)
+        return raw[1:].view(t.shape)
+
+    got = []
+    for odd in ((), ("q",), ("k",), ("v",), ("q", "k", "v", "g", "beta")):
+        pool = gpu_pool_from(ref, D)
+        a = {n: shifted(t) if n in odd else t for n, t in inp.items()}
+        o = fn(pool, 0, dev_i32(np.arange(B)), a["q"], a["k"], a["v"], a["g"], a["beta"])
+        got.append((o.cpu().numpy(), pool.buffer.cpu().numpy().view(np.float32)))
+    for o, s in got[1:]:
+        assert rel_l2(o, got[0][0]) <= 1e-5 and rel_l2(s, got[0][1]) <= 1e-5
+
+
+@pytest.mark.parametrize("kda", [False, True])
+@pytest.mark.parametrize("what", ["v", "k", "q"])
+def test_prefill_nonfinite_input_leaves_earlier_tokens(kda, what):
+    """An infinite input value at one token: every earlier token's output, and
+    for v and q everything the recurrence does not reach (other columns;
+    later tokens and the state), is what it is without it."""
+    d, HK, HV, B, T, at = 128, 1, 1, 1, 40, 21
+    seed = 795
+    ref = orc.Pool(orc.KIND_FP32, d, d, 0, 1, B, HV)
+    orc.pack(ref, 0, np.arange(B), inputs.synthetic_states(seed, B, HV, d))
+    inp = inputs.as_prefill(inputs.decode_inputs(seed, T, B, HK, HV, d, kda=kda))
+    fn = D.damp_state_prefill_kda if kda else D.damp_state_prefill_gdn
+    res = []
+    for bad in (False, True):
+        x = {n: a.copy() for n, a in inp.items()}
+        if bad:
+            x[what][0, at, 0, 37] = 0x7f80  # +inf
+        pool = gpu_pool_from(ref, D)
+        a = dev_inputs(x)
+        o = fn(pool, 0, dev_i32(np.arange(B)), a["q"], a["k"], a["v"], a["g"], a["beta"])
+        res.append((o[0, :, 0].cpu().numpy(),
+                    pool.buffer.cpu().numpy().view(np.float32).reshape(-1)[:d * d].reshape(d, d)))
+    (o0, s0), (o1, s1) = res
+    assert rel_l2(o1[:at], o0[:at]) <= 1e-5
+    assert not np.isfinite(o1[at]).all()
+    if what == "v":  # its column from there on, no other
+        keep = np.arange(d) != 37
+        assert rel_l2(o1[:, keep], o0[:, keep]) <= 1e-5
+        assert rel_l2(s1[:, keep], s0[:, keep]) <= 1e-5
+        assert not np.isfinite(s1[:, 37]).any()
+    if what == "q":
+        keep = np.arange(T) != at
+        assert rel_l2(o1[keep], o0[keep]) <= 1e-5 and rel_l2(s1, s0) <= 1e-5
