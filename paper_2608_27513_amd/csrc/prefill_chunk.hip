@@ -140,22 +140,39 @@ __device__ __forceinline__ Split8 split8(const float* x) {
   return s;
 }
 
-// c + a b over split factors, smallest products first: three when a is exact
-// (NA = 1), the six above 2^-26 of the largest otherwise.
+// big + small + a b over split factors, the product of the leading parts into
+// big and the others into small (three in all when a is exact, NA = 1, else the
+// six above 2^-26 of the largest), so that big is rounded once per call.
+template <int NA>
+__device__ __forceinline__ void mfma32_split(const u4v* a, const Split8& b, f16v& big,
+                                             f16v& small) {
+  if constexpr (NA == 1) {
+    small = mfma32(a[0], b.part[2], small);
+    small = mfma32(a[0], b.part[1], small);
+  } else {
+    small = mfma32(a[2], b.part[0], small);
+    small = mfma32(a[0], b.part[2], small);
+    small = mfma32(a[1], b.part[1], small);
+    small = mfma32(a[1], b.part[0], small);
+    small = mfma32(a[0], b.part[1], small);
+  }
+  big = mfma32(a[0], b.part[0], big);
+}
+// c + a b into one accumulator, smallest products first.
 template <int NA>
 __device__ __forceinline__ f16v mfma32_split(const u4v* a, const Split8& b, f16v c) {
+  f16v s = c;
   if constexpr (NA == 1) {
-    c = mfma32(a[0], b.part[2], c);
-    c = mfma32(a[0], b.part[1], c);
-    return mfma32(a[0], b.part[0], c);
+    s = mfma32(a[0], b.part[2], s);
+    s = mfma32(a[0], b.part[1], s);
   } else {
-    c = mfma32(a[2], b.part[0], c);
-    c = mfma32(a[0], b.part[2], c);
-    c = mfma32(a[1], b.part[1], c);
-    c = mfma32(a[1], b.part[0], c);
-    c = mfma32(a[0], b.part[1], c);
-    return mfma32(a[0], b.part[0], c);
+    s = mfma32(a[2], b.part[0], s);
+    s = mfma32(a[0], b.part[2], s);
+    s = mfma32(a[1], b.part[1], s);
+    s = mfma32(a[1], b.part[0], s);
+    s = mfma32(a[0], b.part[1], s);
   }
+  return mfma32(a[0], b.part[0], s);
 }
 
 __device__ __forceinline__ void wave_sync() {
@@ -739,9 +756,9 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
         }
     }
     // [K; Q] S0: accumulators 0..7 are rows k_t, 8..15 rows q_t, t = 8 ph + e
-    f16v acc;
+    f16v acc, low;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+    for (int i = 0; i < 16; ++i) acc[i] = low[i] = 0.0f;
     const int a_at = row_at(m_row, ph);  // piece 2 ks + ph: bits 5 and up xor 2 ks
     Split8 sb;
     u4v fa[NA];
@@ -757,31 +774,33 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
       step_operands(ks);
-      acc = mfma32_split<NA>(fa, sb, acc);
-      if (KDA) __builtin_amdgcn_sched_barrier(0);  // one step's operands at a time: registers
+      mfma32_split<NA>(fa, sb, acc, low);
+      // the operands of one step (GDN: two) at a time: registers
+      if (KDA || (ks & 1)) __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (KDA) __syncthreads();  // tm is there
-    // R = V - G K S0, and the start G Q S0 of O
-    float R[8];
-    if constexpr (KDA) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        R[e] = bf16_lo(vr[e]) - acc[e];
-        acc[e] = 0.0f;
-      }
-    } else {
+    if constexpr (!KDA) {
       uint32_t bad = 0u;
 #pragma unroll
       for (int e = 0; e < 8; ++e) bad |= nonfinite(vr[e]);
       if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad != 0u) != 0, 0)) return false;
+    }
+    // R = V - G K S0; G Q S0 stays in acc[8 + e]
+    float R[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < 8; ++e) {
+      const float w = acc[e] + low[e];
+      acc[8 + e] += low[8 + e];
+      if constexpr (KDA) {
+        R[e] = bf16_lo(vr[e]) - w;
+      } else {
         const float G = ck.G[8 * ph + e];
-        R[e] = fmaf(-G, acc[e], bf16_lo(vr[e]));
-        acc[e] = 0.0f;
+        R[e] = fmaf(-G, w, bf16_lo(vr[e]));
         acc[8 + e] *= G;
       }
     }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) low[i] = 0.0f;
     {
       const Split8 sr = split8(R);
       Split8 tm;
@@ -795,7 +814,12 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
         for (int j = 0; j < 3; ++j)
           tm.part[j] = *reinterpret_cast<const u4v*>(&ck.tm[j][m_row][8 * ph]);
       }
-      acc = mfma32_split<3>(tm.part, sr, acc);
+      low = mfma32_split<3>(tm.part, sr, low);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      acc[8 + e] += low[8 + e];
+      acc[e] = low[e];
     }
     if (p.o) {
       const int o_row = kD * static_cast<int>(o_esize), step = p.HV * o_row;
