@@ -28,6 +28,8 @@ namespace damp {
 namespace {
 
 constexpr int kCalibThreads = 256;
+constexpr int kPairs = 8;      // row samples a workgroup evaluates per round
+constexpr int kTermPitch = 130;  // doubles of a row sample's terms: the eight rows' sums read distinct banks
 
 struct CalibParams {
   const uint8_t* layer_base;
@@ -43,6 +45,7 @@ struct CalibParams {
   double* count;         // this domain's sample count
   int32_t B;
   int32_t num_slots;
+  int32_t rows;          // tile rows of a workgroup: kPairs / samples per round
   int32_t H;
   int32_t dk;
   int32_t dv;
@@ -74,24 +77,16 @@ __device__ __forceinline__ double sq_term(float xh, float x) {
   return __dmul_rn(e, e);
 }
 
-// Extrema over the lanes whose bit `span` and above agree (span = 64: the
-// wave, 32: each half).
+// Extrema over aligned groups of SPAN lanes (32 or 64).
 template <int SPAN>
 __device__ __forceinline__ void lane_minmax(float& lo, float& hi) {
+  group_minmax<16>(lo, hi);
 #pragma unroll
-  for (int m = 1; m < SPAN; m <<= 1) {
+  for (int m = 16; m < SPAN; m <<= 1) {
     lo = fminf(lo, __shfl_xor(lo, m, 64));
     hi = fmaxf(hi, __shfl_xor(hi, m, 64));
   }
 }
-
-// Per-wave scratch for the statistics of one row sample (d_v <= 128).
-struct RowScratch {
-  float x[128];   // the row
-  float yh[128];  // paper tiers with the transform: the reconstruction, transformed domain
-  double te[128];  // per column: (Q_lo(x) - x)^2
-  double tn[128];  // per column: x^2
-};
 
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
@@ -99,65 +94,84 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
-// || Q_lo(x) - x ||^2 and || x ||^2 of one row by one wave, a lane per column
-// (columns lane, lane + 64). Every per-column operation is written out as
-// the definition: the row's (or, for the paper's tiers, each group of 32's)
-// s and z of Eq. (3) with IEEE division, the FP16 rounding of the stored
-// group (s, z), the normalized block-32 transform as its direct sum over
-// ascending j, and the reconstruction s (c - z). The extrema are order-free;
-// the two sums over the columns run in ascending column order in one lane
-// each (lanes 0 and 32). Returns the sums in those two lanes.
-__device__ void row_stats_wave(const float* xrow, int dv, bool paper, bool had, RowScratch& sc,
-                               int lane, double& err, double& en) {
-  for (int j = lane; j < dv; j += 64) sc.x[j] = xrow[j];
-  wave_sync();
+// Scratch of one wave: the row, and with the block-32 transform its
+// reconstruction in the transformed domain (d_v <= 128).
+struct alignas(16) RowScratch {
+  float x[128];
+  float yh[128];
+};
+
+// The lane's row of the 32 x 32 Sylvester matrix (entries +-1).
+struct SignRow {
+  float s[32];
+};
+__device__ __forceinline__ SignRow sign_row(int lane) {
+  SignRow r;
+#pragma unroll
+  for (int j = 0; j < 32; ++j) r.s[j] = (__builtin_popcount(lane & 31 & j) & 1) ? -1.0f : 1.0f;
+  return r;
+}
+// The direct sum over ascending j of the entries times the 32 values at v,
+// starting from zero: a product with +-1 is exact, so each step rounds as the
+// addition or subtraction of the definition does.
+__device__ __forceinline__ float sylvester(const SignRow& r, const float* v) {
+  float acc = 0.0f;
+#pragma unroll
+  for (int j = 0; j < 32; j += 4) {
+    const float4 x = *reinterpret_cast<const float4*>(v + j);
+    acc = fmaf(x.x, r.s[j], acc);
+    acc = fmaf(x.y, r.s[j + 1], acc);
+    acc = fmaf(x.z, r.s[j + 2], acc);
+    acc = fmaf(x.w, r.s[j + 3], acc);
+  }
+  return acc;
+}
+
+// The terms (Q_lo(x) - x)^2 and x^2 of one row, by one wave, a lane per column
+// (columns lane, lane + 64), into te and tn. Every per-column operation is
+// written out as the definition: the row's (or, for the paper's tiers, each
+// group of 32's) s and z of Eq. (3) with IEEE division, the FP16 rounding of
+// the stored group (s, z), the normalized block-32 transform as its direct sum
+// over ascending j, and the reconstruction s (c - z). The extrema are
+// order-free.
+__device__ __forceinline__ void row_terms(const float (&xv)[2], int dv, bool paper, bool had,
+                                          const SignRow& sg, RowScratch& sc, int lane, double* te,
+                                          double* tn) {
+  bool on[2];
+  float y[2], xh[2];
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    on[m] = lane + 64 * m < dv;
+    y[m] = on[m] ? xv[m] : 0.0f;
+  }
   if (!paper) {
     float lo = INFINITY, hi = -INFINITY;
-    for (int j = lane; j < dv; j += 64) {
-      lo = fminf(lo, sc.x[j]);
-      hi = fmaxf(hi, sc.x[j]);
-    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+      if (on[m]) {
+        lo = fminf(lo, y[m]);
+        hi = fmaxf(hi, y[m]);
+      }
     lane_minmax<64>(lo, hi);
     const float s = qscale_exact(lo, hi);
     const float z = rintf(__fdiv_rn(-lo, s));
-    for (int j = lane; j < dv; j += 64) {
-      const float xv = sc.x[j];
-      sc.te[j] = sq_term(decode_exact(xv, s, z), xv);
-      sc.tn[j] = __dmul_rn(static_cast<double>(xv), static_cast<double>(xv));
-    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m) xh[m] = decode_exact(y[m], s, z);
   } else {
-    // lane holds output i = j % 32 of group j / 32, for j = lane + 64 m; the
-    // 32 lanes of a half-wave hold one group
-    float y[2], yh[2];
-    const int nm = (dv + 63) / 64;
+    // the 32 lanes of a half-wave hold one group
+    if (had) {
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const int j = lane + 64 * m;
-      if (m >= nm || j >= dv) {
-        y[m] = 0.0f;
-        continue;
-      }
-      const int base = j & ~31, i = j & 31;
-      if (had) {
-        float acc = 0.0f;
-        for (int jj = 0; jj < 32; ++jj)
-          acc = (__builtin_popcount(static_cast<unsigned>(i & jj)) & 1) ? __fsub_rn(acc, sc.x[base + jj])
-                                                                        : __fadd_rn(acc, sc.x[base + jj]);
-        y[m] = __fmul_rn(acc, kInvSqrt32);
-      } else {
-        y[m] = sc.x[j];
-      }
+      for (int m = 0; m < 2; ++m)
+        if (on[m]) sc.x[lane + 64 * m] = y[m];
+      wave_sync();
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+        if (on[m]) y[m] = __fmul_rn(sylvester(sg, &sc.x[(lane & ~31) + 64 * m]), kInvSqrt32);
     }
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
-      const int j = lane + 64 * m;
-      const bool on = m < nm && j < dv;
-      float lo = on ? y[m] : INFINITY, hi = on ? y[m] : -INFINITY;
+      float lo = y[m], hi = y[m];
       lane_minmax<32>(lo, hi);
-      if (!on) {
-        yh[m] = 0.0f;
-        continue;
-      }
       const float s = qscale_exact(lo, hi);
       float s16 = round_f16(s);
       if (!(s16 > 0.0f)) s16 = 5.9604644775390625e-08f;  // smallest positive FP16
@@ -165,104 +179,119 @@ __device__ void row_stats_wave(const float* xrow, int dv, bool paper, bool had, 
       float zf = rintf(__fdiv_rn(-lo, s16));
       if (zf > 65504.0f) zf = 65504.0f;
       if (zf < -65504.0f) zf = -65504.0f;
-      const float z16 = round_f16(zf);
-      yh[m] = decode_exact(y[m], s16, z16);
+      xh[m] = decode_exact(y[m], s16, round_f16(zf));
     }
-    if (had) {
-      for (int m = 0; m < nm; ++m) {
-        const int j = lane + 64 * m;
-        if (j < dv) sc.yh[j] = yh[m];
-      }
+    if (had) {  // back from the transformed domain, the same direct sum
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+        if (on[m]) sc.yh[lane + 64 * m] = xh[m];
       wave_sync();
-    }
-    for (int m = 0; m < nm; ++m) {
-      const int j = lane + 64 * m;
-      if (j >= dv) continue;
-      float xh = yh[m];
-      if (had) {  // back from the transformed domain, the same direct sum
-        const int base = j & ~31, i = j & 31;
-        float acc = 0.0f;
-        for (int jj = 0; jj < 32; ++jj)
-          acc = (__builtin_popcount(static_cast<unsigned>(i & jj)) & 1) ? __fsub_rn(acc, sc.yh[base + jj])
-                                                                        : __fadd_rn(acc, sc.yh[base + jj]);
-        xh = __fmul_rn(acc, kInvSqrt32);
-      }
-      const float xv = sc.x[j];
-      sc.te[j] = sq_term(xh, xv);
-      sc.tn[j] = __dmul_rn(static_cast<double>(xv), static_cast<double>(xv));
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+        if (on[m]) xh[m] = __fmul_rn(sylvester(sg, &sc.yh[(lane & ~31) + 64 * m]), kInvSqrt32);
+      wave_sync();  // the scratch is reused by the wave's next row
     }
   }
-  wave_sync();
-  // ascending sums: lane 0 the error terms, lane 32 the energies
-  double acc = 0.0;
-  if (lane == 0 || lane == 32) {
-    const double* src = lane == 0 ? sc.te : sc.tn;
-    for (int j = 0; j < dv; ++j) acc = __dadd_rn(acc, src[j]);
-  }
-  err = acc;
-  en = acc;
-  wave_sync();  // the scratch is reused by the wave's next sample
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+    if (on[m]) {
+      te[lane + 64 * m] = sq_term(xh[m], xv[m]);
+      tn[lane + 64 * m] = __dmul_rn(static_cast<double>(xv[m]), static_cast<double>(xv[m]));
+    }
 }
 
-// One workgroup per (head, tile row). Its four waves evaluate up to 256
-// samples at a time, one sample per wave at a time, into LDS; thread 0 then
-// adds them to the accumulators in sample order, continuing from the values
-// already stored.
+// Terms of up to kPairs row samples and their sums.
+struct PairTerms {
+  double t[2][kPairs][kTermPitch];  // error and energy terms by column
+  double sum[2][kPairs];
+};
+// Ascending sums over the columns, from zero: thread 2 i + w < 2 kPairs sums
+// row sample i's terms w.
+__device__ __forceinline__ void sum_terms(PairTerms& pt, int thread, int dv) {
+  if (thread >= 2 * kPairs) return;
+  const double* src = pt.t[thread & 1][thread >> 1];
+  double acc = 0.0;
+  for (int j = 0; j < dv; j += 8) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc = __dadd_rn(acc, src[j + u]);
+  }
+  pt.sum[thread & 1][thread >> 1] = acc;
+}
+
+// One workgroup per p.rows tile rows of a head. A round evaluates kPairs row
+// samples, p.rows rows of kPairs / p.rows consecutive requests, two per wave;
+// 2 kPairs lanes then form their sums over the columns side by side, and
+// thread r < p.rows adds row r's to its accumulators in sample order,
+// continuing from the values already stored. What bounds it is the length of
+// that chain, not the work: with one request (8 rows a workgroup) 4096 rows
+// take two row evaluations a wave and one pass of the serial sums. Before, a
+// workgroup had one row, whose one sample left three of its waves idle:
+// 30 -> 8 us at 32 heads, d = 128 and the H32 tier.
 __global__ __launch_bounds__(kCalibThreads) void calib_accumulate_kernel(const CalibParams p) {
-  __shared__ double se[kCalibThreads], sn[kCalibThreads], sl[kCalibThreads];
-  __shared__ int sv[kCalibThreads];
+  __shared__ PairTerms pt;
   __shared__ RowScratch scr[kCalibThreads / 64];
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int h = blockIdx.x / p.dk;
-  const int r = blockIdx.x % p.dk;
-  const int u = p.perm ? static_cast<int>(p.perm[static_cast<size_t>(h) * p.dk + r]) : r;
+  const int rows = p.rows, per = kPairs / rows;
+  const int h = blockIdx.x * rows / p.dk;
+  const int r0 = blockIdx.x * rows % p.dk;
+  const uint8_t* perm = p.perm ? p.perm + static_cast<size_t>(h) * p.dk : nullptr;
+  const SignRow sg = sign_row(lane);
+  const int u = t < rows ? (perm ? static_cast<int>(perm[r0 + t]) : r0 + t) : 0;
   const size_t hu = static_cast<size_t>(h) * p.dk + u;
   double acc_e = 0.0, acc_n = 0.0, acc_l = 0.0, nvalid = 0.0;
-  if (t == 0) {
+  if (t < rows) {
     acc_e = p.err[hu];
     acc_n = p.en[hu];
     acc_l = p.loga[hu];
   }
-  for (int b0 = 0; b0 < p.B; b0 += kCalibThreads) {
-    const int n = min(kCalibThreads, p.B - b0);
-    for (int i = wave; i < n; i += kCalibThreads / 64) {
-      const int b = b0 + i;
-      const int slot = p.slot_idx[b];
-      const bool valid = slot >= 0 && slot < p.num_slots;
-      if (valid) {
-        const float* x = reinterpret_cast<const float*>(
+  for (int b0 = 0; b0 < p.B; b0 += per) {
+    // pair i: row i % rows of request b0 + i / rows
+    float x[kPairs / 4][2];
+    bool live[kPairs / 4];
+#pragma unroll
+    for (int k = 0; k < kPairs / 4; ++k) {
+      const int i = wave + 4 * k, b = b0 + i / rows;
+      const int slot = b < p.B ? p.slot_idx[b] : -1;
+      live[k] = slot >= 0 && slot < p.num_slots;
+      x[k][0] = x[k][1] = 0.0f;
+      if (live[k]) {
+        const float* row = reinterpret_cast<const float*>(
             p.layer_base + static_cast<size_t>(slot) * p.slot_stride +
-            static_cast<size_t>(h) * p.tile_stride) + static_cast<size_t>(r) * p.dv;
-        double e = 0.0, e2 = 0.0;
-        row_stats_wave(x, p.dv, p.paper != 0, p.had != 0, scr[wave], lane, e, e2);
-        if (lane == 0) {
-          se[i] = e;
-          const uint16_t gb = p.is_kda ? p.g[b * p.g_bstride + static_cast<int64_t>(h) * p.dk + u]
-                                       : p.g[b * p.g_bstride + h];
-          sl[i] = static_cast<double>(bf16_to_f32(gb));
-        }
-        if (lane == 32) sn[i] = e2;
+            static_cast<size_t>(h) * p.tile_stride) + static_cast<size_t>(r0 + i % rows) * p.dv;
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+          if (lane + 64 * m < p.dv) x[k][m] = row[lane + 64 * m];
       }
-      if (lane == 0) sv[i] = valid ? 1 : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < kPairs / 4; ++k) {
+      const int i = wave + 4 * k;
+      if (live[k])
+        row_terms(x[k], p.dv, p.paper != 0, p.had != 0, sg, scr[wave], lane, pt.t[0][i], pt.t[1][i]);
     }
     __syncthreads();
-    if (t == 0) {
-      for (int i = 0; i < n; ++i) {
-        if (!sv[i]) continue;
-        acc_e = __dadd_rn(acc_e, se[i]);
-        acc_n = __dadd_rn(acc_n, sn[i]);
-        acc_l = __dadd_rn(acc_l, sl[i]);
+    sum_terms(pt, t, p.dv);
+    wave_sync();  // the sums and what adds them are one wave's
+    if (t < rows) {
+      for (int k = 0; k < per && b0 + k < p.B; ++k) {
+        const int b = b0 + k, slot = p.slot_idx[b];
+        if (slot < 0 || slot >= p.num_slots) continue;
+        const uint16_t gb = p.is_kda ? p.g[b * p.g_bstride + static_cast<int64_t>(hu)]
+                                     : p.g[b * p.g_bstride + h];
+        acc_e = __dadd_rn(acc_e, pt.sum[0][k * rows + t]);
+        acc_n = __dadd_rn(acc_n, pt.sum[1][k * rows + t]);
+        acc_l = __dadd_rn(acc_l, static_cast<double>(bf16_to_f32(gb)));
         nvalid += 1.0;
       }
     }
     __syncthreads();
   }
-  if (t == 0) {
+  if (t < rows) {
     p.err[hu] = acc_e;
     p.en[hu] = acc_n;
     p.loga[hu] = acc_l;
-    if (blockIdx.x == 0) *p.count = __dadd_rn(*p.count, nvalid);
+    if (blockIdx.x == 0 && t == 0) *p.count = __dadd_rn(*p.count, nvalid);
   }
 }
 
@@ -311,7 +340,10 @@ damp_status accumulate(const damp_calib* c, int32_t domain, const damp_pool* poo
   p.is_kda = c->is_kda;
   p.paper = layout_is_paper(&c->lo) ? 1 : 0;
   p.had = c->lo.hadamard;
-  hipLaunchKernelGGL(calib_accumulate_kernel, dim3(static_cast<unsigned>(hk)),
+  // rows of a workgroup: fewer requests than kPairs leave room for more rows
+  p.rows = kPairs;
+  while (p.rows > 1 && kPairs / p.rows < B) p.rows /= 2;
+  hipLaunchKernelGGL(calib_accumulate_kernel, dim3(static_cast<unsigned>(hk / p.rows)),
                      dim3(kCalibThreads), 0, stream, p);
   return check_launch("damp_calib_accumulate");
 }
@@ -334,19 +366,33 @@ damp_status check_fp32_pool(const damp_calib* c, const damp_pool* pool, int32_t 
 }
 
 // || Q_lo(x) - x ||^2 of independent rows (row i at states + i * dv) under
-// the paper's UINT8 group tier, one row per wave, the same per-row
+// the paper's UINT8 group tier, kPairs rows per workgroup, the same per-row
 // evaluation as the accumulation above.
-__global__ __launch_bounds__(256) void row_error_group_kernel(const float* __restrict__ states,
-                                                              int64_t rows, int dv, int had,
-                                                              double* __restrict__ err) {
-  __shared__ RowScratch scr[4];
+__global__ __launch_bounds__(kCalibThreads) void row_error_group_kernel(
+    const float* __restrict__ states, int64_t rows, int dv, int had, double* __restrict__ err) {
+  __shared__ PairTerms pt;
+  __shared__ RowScratch scr[kCalibThreads / 64];
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + wave;
-  if (row >= rows) return;  // whole waves leave: the evaluation synchronises within a wave only
-  double e = 0.0, e2 = 0.0;
-  row_stats_wave(states + row * dv, dv, true, had != 0, scr[wave], lane, e, e2);
-  if (lane == 0) err[row] = e;
+  const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kPairs;
+  const SignRow sg = sign_row(lane);
+  float x[kPairs / 4][2];
+#pragma unroll
+  for (int k = 0; k < kPairs / 4; ++k) {
+    const int64_t row = row0 + wave + 4 * k;
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+      x[k][m] = row < rows && lane + 64 * m < dv ? states[row * dv + lane + 64 * m] : 0.0f;
+  }
+#pragma unroll
+  for (int k = 0; k < kPairs / 4; ++k) {
+    const int i = wave + 4 * k;
+    if (row0 + i < rows)
+      row_terms(x[k], dv, true, had != 0, sg, scr[wave], lane, pt.t[0][i], pt.t[1][i]);
+  }
+  __syncthreads();
+  sum_terms(pt, t, dv);
+  if (t < 2 * kPairs && (t & 1) == 0 && row0 + (t >> 1) < rows) err[row0 + (t >> 1)] = pt.sum[0][t >> 1];
 }
 
 // Average ranks (ties share the mean of their positions), 1-based.
@@ -369,9 +415,9 @@ std::vector<double> ranks_of(const double* x, int n) {
 
 void launch_row_errors_group(const float* states, int64_t rows, int dv, bool had, double* err,
                              hipStream_t stream) {
-  const int64_t blocks = (rows + 3) / 4;
-  hipLaunchKernelGGL(row_error_group_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0,
-                     stream, states, rows, dv, had ? 1 : 0, err);
+  const int64_t blocks = (rows + kPairs - 1) / kPairs;
+  hipLaunchKernelGGL(row_error_group_kernel, dim3(static_cast<unsigned>(blocks)),
+                     dim3(kCalibThreads), 0, stream, states, rows, dv, had ? 1 : 0, err);
 }
 
 }  // namespace damp

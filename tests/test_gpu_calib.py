@@ -88,6 +88,32 @@ def test_accumulate_and_finalize_are_bit_exact(kda, fmt, d):
             assert np.array_equal(got[name].numpy(), want[name]), (sel, name)
 
 
+@pytest.mark.parametrize("kda,fmt,d", [(True, orc.FMT_PAPER, 128), (False, None, 16)])
+@pytest.mark.parametrize("B", [1, 2, 3, 4, 7, 8, 9, 17])
+def test_accumulate_batches_are_bit_exact(kda, fmt, d, B):
+    """A workgroup evaluates eight row samples at a time: eight rows of one
+    request down to one row of eight, so every split of a batch, a partial
+    last round, and a padded request in it."""
+    H, seed = 2, 840 + B
+    cal = D.Calib(_layout(d, fmt), kda=kda, num_heads=H)
+    ref = orc.Calib(kda=kda, H=H, dk=d, dv=d, fmt=fmt)
+    S = inputs.synthetic_states(seed, B, H, d)
+    perm = inputs.random_perms(seed, H, d)
+    slots = np.random.default_rng(seed).permutation(B + 2)[:B].astype(np.int32)
+    gpool = _fp32_pool(S, perm, slots, B + 2)
+    shape = (B, H, d) if kda else (B, H)
+    g = inputs.to_bf16_bits(-np.abs(np.random.default_rng(seed).standard_normal(shape)))
+    keep = np.arange(B) != (2 if B > 2 else -1)
+    slots_dev = np.where(keep, slots, B + 2).astype(np.int32)  # one past the pool: skipped
+    for _ in range(2):
+        D.damp_calib_accumulate(cal, 0, gpool, 0, dev_i32(slots_dev),
+                                torch.from_numpy(g.view(np.int16)).cuda().view(torch.bfloat16),
+                                perm=dev_u8(perm))
+        ref.accumulate(0, S[keep], g[keep])
+    sums, counts = _device_sums(cal)
+    assert np.array_equal(counts, ref.counts) and np.array_equal(sums, ref.sums)
+
+
 def _valid_topk(sel, score, k, rtol):
     """sel (per head) is a top-k of score up to rtol: every kept channel
     scores at least the k-th largest score less rtol of it."""
