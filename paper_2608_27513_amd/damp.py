@@ -127,6 +127,24 @@ def _stream(stream=None):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+def _raw_stream(stream=None) -> int:
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
+
+
+def _at(t, dtype, name: str, shape) -> int:
+    """The address of a device tensor of this type and shape. Checked here with
+    as few calls as it takes (a decode step's kernel is shorter than the checks
+    of its operands were); what does not pass goes to _dev for its message."""
+    try:
+        if t.is_cuda and t.dtype is dtype and t.shape == shape and t.is_contiguous():
+            return t.data_ptr()
+    except AttributeError:
+        pass
+    return _dev(t, dtype, name, shape).data_ptr()
+
+
 def _dev(t: torch.Tensor, dtype, name: str, shape=None) -> torch.Tensor:
     if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
         raise ValueError(f"{name} must be a CUDA (HIP) tensor")
@@ -218,29 +236,26 @@ def damp_pool_reset_slots(pool: Pool, layer: int, slots: torch.Tensor, stream=No
 def _update_args(kda: bool, pool: Pool, layer: int, slot_idx, q, k, v, g, beta, perm, scale,
                  o, stream):
     """Checks the operands and returns (C function, argument tuple)."""
-    d = pool.d
+    d = pool.layout.d_k
     HV = pool.num_v_heads
-    slot_idx = _dev(slot_idx, torch.int32, "slot_idx")
+    _dev(slot_idx, torch.int32, "slot_idx")
     B = slot_idx.numel()
     HK = q.shape[1] if q.dim() == 3 else -1
-    _dev(q, torch.bfloat16, "q", (B, HK, d))
-    _dev(k, torch.bfloat16, "k", (B, HK, d))
-    _dev(v, torch.bfloat16, "v", (B, HV, d))
-    _dev(g, torch.bfloat16, "g", (B, HV, d) if kda else (B, HV))
-    _dev(beta, torch.bfloat16, "beta", (B, HV))
-    if perm is not None:
-        _dev(perm, torch.uint8, "perm", (HV, d))
-    if o.dtype == torch.float32:
+    kq, vo, bf16 = (B, HK, d), (B, HV, d), torch.bfloat16
+    if o.dtype is torch.float32:
         o_dt = DAMP_DT_FP32
-    elif o.dtype == torch.bfloat16:
+    elif o.dtype is bf16:
         o_dt = DAMP_DT_BF16
     else:
+        o_dt = -1
+    args = [ctypes.byref(pool.desc), layer, slot_idx.data_ptr(), B, HK, _at(q, bf16, "q", kq),
+            _at(k, bf16, "k", kq), _at(v, bf16, "v", vo),
+            _at(g, bf16, "g", vo if kda else (B, HV)), _at(beta, bf16, "beta", (B, HV)),
+            None if perm is None else _at(perm, torch.uint8, "perm", (HV, d)), float(scale)]
+    if o_dt < 0:
         raise ValueError("o must be float32 or bfloat16")
-    _dev(o, o.dtype, "o", (B, HV, d))
-    fn = lib().damp_state_update_kda if kda else lib().damp_state_update_gdn
-    args = (ctypes.byref(pool.desc), layer, _ptr(slot_idx), B, HK, _ptr(q), _ptr(k), _ptr(v),
-            _ptr(g), _ptr(beta), _ptr(perm), float(scale), _ptr(o), o_dt, _stream(stream))
-    return fn, args
+    args += (_at(o, o.dtype, "o", vo), o_dt, _raw_stream(stream))
+    return (lib().damp_state_update_kda if kda else lib().damp_state_update_gdn), args
 
 
 def _update(kda: bool, pool: Pool, layer: int, slot_idx, q, k, v, g, beta, perm, scale, o,
@@ -277,25 +292,21 @@ def _prefill(kda: bool, pool: Pool, layer: int, slot_idx, q, k, v, g, beta, perm
     if q.dim() != 4:
         raise ValueError("q must be [B, T, HK, d]")
     T, HK = q.shape[1], q.shape[2]
-    _dev(q, torch.bfloat16, "q", (B, T, HK, d))
-    _dev(k, torch.bfloat16, "k", (B, T, HK, d))
-    _dev(v, torch.bfloat16, "v", (B, T, HV, d))
-    _dev(g, torch.bfloat16, "g", (B, T, HV, d) if kda else (B, T, HV))
-    _dev(beta, torch.bfloat16, "beta", (B, T, HV))
-    if perm is not None:
-        _dev(perm, torch.uint8, "perm", (HV, d))
+    kq, vo, bf16 = (B, T, HK, d), (B, T, HV, d), torch.bfloat16
+    args = [ctypes.byref(pool.desc), layer, slot_idx.data_ptr(), B, T, HK, _at(q, bf16, "q", kq),
+            _at(k, bf16, "k", kq), _at(v, bf16, "v", vo),
+            _at(g, bf16, "g", vo if kda else (B, T, HV)), _at(beta, bf16, "beta", (B, T, HV)),
+            None if perm is None else _at(perm, torch.uint8, "perm", (HV, d)), float(scale)]
     if o is None:
-        o = torch.empty((B, T, HV, d), dtype=torch.float32, device=pool.buffer.device)
-    if o.dtype == torch.float32:
+        o = torch.empty(vo, dtype=torch.float32, device=pool.buffer.device)
+    if o.dtype is torch.float32:
         o_dt = DAMP_DT_FP32
-    elif o.dtype == torch.bfloat16:
+    elif o.dtype is bf16:
         o_dt = DAMP_DT_BF16
     else:
         raise ValueError("o must be float32 or bfloat16")
-    _dev(o, o.dtype, "o", (B, T, HV, d))
     fn = lib().damp_state_prefill_kda if kda else lib().damp_state_prefill_gdn
-    _check(fn(ctypes.byref(pool.desc), layer, _ptr(slot_idx), B, T, HK, _ptr(q), _ptr(k), _ptr(v),
-              _ptr(g), _ptr(beta), _ptr(perm), float(scale), _ptr(o), o_dt, _stream(stream)))
+    _check(fn(*args, _at(o, o.dtype, "o", vo), o_dt, _raw_stream(stream)))
     return o
 
 
@@ -315,27 +326,27 @@ def damp_state_prefill_kda(pool: Pool, layer: int, slot_idx, q, k, v, g, beta, p
 
 # ----------------------------------------------------------- pack / unpack
 
+def _exchange_args(pool: Pool, slot_idx, perm):
+    """Slots and permutation of pack and unpack: (state shape, perm address)."""
+    _dev(slot_idx, torch.int32, "slot_idx")
+    d, HV = pool.layout.d_k, pool.num_v_heads
+    return ((slot_idx.numel(), HV, d, d),
+            None if perm is None else _at(perm, torch.uint8, "perm", (HV, d)))
+
+
 def damp_state_pack(pool: Pool, layer: int, slot_idx, S, perm=None, stream=None) -> None:
-    slot_idx = _dev(slot_idx, torch.int32, "slot_idx")
-    d = pool.d
-    _dev(S, torch.float32, "S", (slot_idx.numel(), pool.num_v_heads, d, d))
-    if perm is not None:
-        _dev(perm, torch.uint8, "perm", (pool.num_v_heads, d))
-    _check(lib().damp_state_pack(ctypes.byref(pool.desc), layer, _ptr(slot_idx),
-                                 slot_idx.numel(), _ptr(S), _ptr(perm), _stream(stream)))
+    shape, perm_at = _exchange_args(pool, slot_idx, perm)
+    _check(lib().damp_state_pack(ctypes.byref(pool.desc), layer, slot_idx.data_ptr(), shape[0],
+                                 _at(S, torch.float32, "S", shape), perm_at, _raw_stream(stream)))
 
 
 def damp_state_unpack(pool: Pool, layer: int, slot_idx, perm=None, S_out=None, stream=None):
-    slot_idx = _dev(slot_idx, torch.int32, "slot_idx")
-    d = pool.d
-    shape = (slot_idx.numel(), pool.num_v_heads, d, d)
+    shape, perm_at = _exchange_args(pool, slot_idx, perm)
     if S_out is None:
         S_out = torch.empty(shape, dtype=torch.float32, device=pool.buffer.device)
-    _dev(S_out, torch.float32, "S_out", shape)
-    if perm is not None:
-        _dev(perm, torch.uint8, "perm", (pool.num_v_heads, d))
-    _check(lib().damp_state_unpack(ctypes.byref(pool.desc), layer, _ptr(slot_idx),
-                                   slot_idx.numel(), _ptr(perm), _ptr(S_out), _stream(stream)))
+    _check(lib().damp_state_unpack(ctypes.byref(pool.desc), layer, slot_idx.data_ptr(), shape[0],
+                                   perm_at, _at(S_out, torch.float32, "S_out", shape),
+                                   _raw_stream(stream)))
     return S_out
 
 

@@ -11,6 +11,7 @@ import re
 import numpy as np
 import pytest
 import scipy.stats
+import torch
 
 from oracle import oracle as orc
 from paper_2608_27513_amd import damp as D
@@ -389,3 +390,11 @@ def test_calib_validation_fails_before_launch(L):
         D.DAMP_ERR_INVALID_ARG
     assert fin(ctypes.byref(cal), D.DAMP_SEL_RANDOM, 16, 1e-4, None, sel, perm, None, None,
                None) == D.DAMP_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("t", [None, [1.0], torch.zeros(2), torch.zeros(2, dtype=torch.int32)])
+def test_operand_check_refuses_what_is_no_device_tensor(t):
+    """The operands' short check refuses, with the long one's error, whatever
+    is not a device tensor."""
+    with pytest.raises(ValueError, match="x must be a CUDA"):
+        D._at(t, torch.float32, "x", (2,))

@@ -333,3 +333,13 @@ def test_graph_replay_matches_eager_launches():
         assert torch.equal(graphed.buffer, eager.buffer)
         assert torch.equal(o_g, o_e)
     del junk
+
+
+def test_operand_check_refuses_wrong_type_shape_and_layout():
+    """What the operands' short check does not pass is refused by name."""
+    t = torch.zeros((4, 6), dtype=torch.bfloat16, device="cuda")
+    assert D._at(t, torch.bfloat16, "x", (4, 6)) == t.data_ptr()
+    for bad, shape, what in ((t.float(), (4, 6), "must be"), (t, (6, 4), "expected"),
+                             (t.t(), (6, 4), "contiguous")):
+        with pytest.raises(ValueError, match=f"x .*{what}"):
+            D._at(bad, torch.bfloat16, "x", shape)
