@@ -50,14 +50,16 @@
 // three-way splits are half. A wave alone issues one in 5 cycles, and a matrix
 // instruction keeps the SIMD's vector unit from others' use for about 22 of
 // its 32 cycles, so the kernel is held to 168 registers and 51 200 bytes of
-// LDS: three workgroups a CU. A register that spills costs more than it looks
+// LDS: three workgroups a CU. While there are no more tiles than CUs, a
+// workgroup has four more waves that stage the next chunks meanwhile (SPLIT).
+// A register that spills costs more than it looks
 // (its reload waits for every load and store before it: 336 -> 440 us with
 // some ten in the loop), hence opaque() and the scheduling barriers. Chunks of
 // 16: the products within a chunk and T grow with its square.
 // Measured against the token-by-token fp32 kernel before it (two FMAs per
 // value and token for the read-outs, one for the update), GDN, B = 256, 32
-// heads, 64 tokens: 805 -> 320 us; KDA, B = 32, 250 tokens: 498 -> 270 us; GDN,
-// two requests of 1024 tokens: 728 -> 180 us; 2 tokens at B = 256: 154 -> 139 us
+// heads, 64 tokens: 805 -> 319 us; KDA, B = 32, 250 tokens: 498 -> 265 us; GDN,
+// two requests of 1024 tokens: 728 -> 136 us; 2 tokens at B = 256: 154 -> 139 us
 // (GDN), 167 -> 164 us (KDA).
 #include <cfloat>
 #include <cstdint>
@@ -219,17 +221,23 @@ struct alignas(16) ChunkLds<true> {
   int32_t flag[4], vflag[4];  // by staging wave; by wave, its columns of v
 };
 
-template <bool KDA>
+// SPLIT: eight waves a workgroup, four of which stage the next chunks into a
+// second buffer while the others run these.
+template <bool KDA, bool SPLIT>
 struct Prefill {
+  static constexpr int NT = SPLIT ? 512 : 256;
   static constexpr int NC = KDA ? 1 : 4;  // chunks staged together
   static constexpr int NA = KDA ? 3 : 1;
   using Chunk = ChunkLds<KDA>;
   static constexpr size_t kTransit = sizeof(float) * kD * kPitch;
+  static constexpr size_t kStaged = (SPLIT ? 2 : 1) * NC * sizeof(Chunk);
   static constexpr size_t kBytes =
-      NC * sizeof(Chunk) > kTransit ? NC * sizeof(Chunk) : kTransit;
+      SPLIT ? kStaged + kTransit : (kStaged > kTransit ? kStaged : kTransit);
 };
-static_assert(Prefill<true>::kBytes <= 54272 && Prefill<false>::kBytes <= 54272,
-              "three workgroups of a CU share 160 KB of LDS");
+static_assert(Prefill<true, false>::kBytes <= 51200 && Prefill<false, false>::kBytes <= 51200,
+              "three workgroups share a CU's LDS");
+static_assert(Prefill<true, true>::kBytes <= 160 * 1024 && Prefill<false, true>::kBytes <= 160 * 1024,
+              "LDS of a CU");
 
 // (I + A)^-1 by forward substitution, one column per lane (c = lane % 16, the
 // four lanes of a column alike), and the rows of [diag(E) T; B T] for a chunk
@@ -284,16 +292,18 @@ __device__ __forceinline__ void solve_chunk(const float (*ab)[kC], int lane, int
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int KIND, bool KDA>
-__global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p) {
-  using P = Prefill<KDA>;
+template <int KIND, bool KDA, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chunk128(
+    const PrefillParams p) {
+  using P = Prefill<KDA, SPLIT>;
   constexpr int NC = P::NC, NA = P::NA, CPT = 16, TPR = 8;
   __shared__ __attribute__((aligned(16))) uint8_t lds_raw[P::kBytes];
   typename P::Chunk* L = reinterpret_cast<typename P::Chunk*>(lds_raw);
-  float(*tbuf)[kPitch] = reinterpret_cast<float(*)[kPitch]>(lds_raw);
+  float(*tbuf)[kPitch] = reinterpret_cast<float(*)[kPitch]>(lds_raw + (SPLIT ? P::kStaged : 0));
 
-  const int t = threadIdx.x, lane = t & 63;
+  const int t = threadIdx.x & 255, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const bool stages = SPLIT && __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) != 0;
   const int ph = lane >> 5, l32 = lane & 31;  // half: tokens (or channels) 8 ph ..
   const int h = blockIdx.x, b = blockIdx.y;
   const int T = p.T;
@@ -303,7 +313,7 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
   const size_t o_step = static_cast<size_t>(p.HV) * kD * o_esize;
   uint8_t* const o_col = static_cast<uint8_t*>(p.o) +
                          ((static_cast<size_t>(b) * T * p.HV + h) * kD + col) * o_esize;
-  auto write_o = [&](int tok, float val) {
+  auto write_o = [&](int tok, float val) __attribute__((always_inline)) {
     uint8_t* at = o_col + static_cast<size_t>(tok) * o_step;
     if (p.o_bf16) *reinterpret_cast<uint16_t*>(at) = f32_to_bf16(val);
     else *reinterpret_cast<float*>(at) = val;
@@ -311,7 +321,7 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
 
   const int slot = __builtin_amdgcn_readfirstlane(p.slot_idx[b]);
   if (slot < 0 || slot >= p.num_slots) {  // padded request: o = 0, state untouched
-    if (p.o)
+    if (p.o && !stages)
       for (int tok = ph; tok < T; tok += 2) write_o(tok, 0.0f);
     return;
   }
@@ -324,8 +334,8 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
 
   // rows of the inputs: token tok of this request and head
   const size_t tok0 = static_cast<size_t>(b) * p.t_pitch + p.t0;
-  auto k_row = [&](int tok) { return ((tok0 + tok) * p.HK + hk) * kD; };
-  auto v_row = [&](int tok) { return (tok0 + tok) * p.HV + h; };
+  auto k_row = [&](int tok) __attribute__((always_inline)) { return ((tok0 + tok) * p.HK + hk) * kD; };
+  auto v_row = [&](int tok) __attribute__((always_inline)) { return (tok0 + tok) * p.HV + h; };
 
   // ---- inputs of NC chunks, through buffer resources that end with the last
   // token: later tokens read zeros
@@ -337,7 +347,7 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
     uint32_t g, beta;
   } in;
   const int kq_step = p.HK * kRow, v_step = p.HV * kRow;
-  auto load_inputs = [&](int tb0) {
+  auto load_inputs = [&](int tb0) __attribute__((always_inline)) {
     const int lane = opaque(t) & 63, ph = lane >> 5, l32 = lane & 31, col = 32 * wave + l32;
     const int ntok = T - tb0 < NC * kC ? T - tb0 : NC * kC;
     const size_t row = tok0 + tb0;
@@ -376,8 +386,8 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
   };
   // one load per 128-byte line of the rows of the NC chunks from token tb0, so
   // that load_inputs finds them in the L2; the caller drops the values
-  auto touch = [&](int tb0, uint32_t& x0, uint32_t& x1) {
-    const int t = opaque(threadIdx.x);
+  auto touch = [&](int tb0, uint32_t& x0, uint32_t& x1) __attribute__((always_inline)) {
+    const int t = opaque(threadIdx.x & 255);
     const int ntok = T - tb0 < NC * kC ? T - tb0 : NC * kC;
     const size_t row = tok0 + tb0;
     const auto rk = rows_rsrc(p.k + (row * p.HK + hk) * kD, kq_step, kRow, ntok);
@@ -399,8 +409,276 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
     }
   };
 
+  // the lane id, formed anew in each phase (see opaque)
+  auto lane_now = [&]() __attribute__((always_inline)) { return opaque(t) & 63; };
+
+  auto flagged = [&](const typename P::Chunk& ck) __attribute__((always_inline)) -> bool {
+    int f;
+    if constexpr (KDA)
+      f = ck.flag[0] | ck.flag[1] | ck.flag[2] | ck.flag[3] | ck.vflag[0] | ck.vflag[1] |
+          ck.vflag[2] | ck.vflag[3];
+    else
+      f = ck.flag;
+    return __builtin_amdgcn_readfirstlane(f) != 0;
+  };
+
+  // ---- GDN staging, wave-local: wave w stages chunk w
+  auto stage_gdn = [&](typename P::Chunk& ck, int tb) __attribute__((always_inline)) {
+    if constexpr (!KDA) {
+      if (tb >= T) return;
+      const int lane = lane_now();
+      uint32_t bad = 0u;
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        const int row = (lane >> 4) + 4 * i;
+        *reinterpret_cast<u4v*>(ck.kq[0] + row_at(row, lane & 15)) = in.k[i];
+        *reinterpret_cast<u4v*>(ck.kq[0] + row_at(16 + row, lane & 15)) = in.q[i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          bad |= nonfinite(in.k[i][j]) | nonfinite(in.q[i][j]);
+      }
+      const float a = __expf(bf16_to_f32(static_cast<uint16_t>(in.g)));  // 1 past the end
+      const float beta = bf16_to_f32(static_cast<uint16_t>(in.beta));
+      if (!(a <= FLT_MAX) || !(fabsf(beta) <= FLT_MAX)) bad = 1u;
+      const bool any = __builtin_amdgcn_ballot_w64(bad != 0u) != 0;
+      if (lane == 0) ck.flag = any ? 1 : 0;
+      if (lane < kC) {
+        ck.a[lane] = a;
+        ck.beta[lane] = beta;
+      }
+      if (any) return;
+      // decay ratios: this lane's column s, rows t = 4 quad + i
+      const int s = lane & 15, quad = lane >> 4;
+      float Lr[4] = {0.0f, 0.0f, 0.0f, 0.0f}, G = 1.0f, run = 1.0f, Gs = 1.0f;
+#pragma unroll
+      for (int tt = 0; tt < kC; ++tt) {
+        const float at = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), tt));
+        G *= at;
+        if (s == tt) Gs = G;
+        run = tt <= s ? 1.0f : run * at;
+        if (quad == (tt >> 2)) Lr[tt & 3] = run;
+      }
+      if (lane < kC) ck.G[lane] = Gs;
+      const float E = run * beta;  // L_{15,s} beta_s
+      wave_sync();
+      f4v kk = {0.0f, 0.0f, 0.0f, 0.0f}, qk = kk;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const u4v fk = *reinterpret_cast<const u4v*>(ck.kq[0] + row_at(s, 4 * ks + quad));
+        const u4v fq = *reinterpret_cast<const u4v*>(ck.kq[0] + row_at(16 + s, 4 * ks + quad));
+        kk = mfma16(fk, fk, kk);
+        qk = mfma16(fq, fk, qk);
+      }
+      float(*ab)[kC] = reinterpret_cast<float(*)[kC]>(ck.tm);
+      float e4[4], um[4], om[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int tt = 4 * quad + i;
+        const float f = Lr[i] * beta;
+        ab[tt][s] = s < tt ? f * kk[i] : 0.0f;
+        ab[16 + tt][s] = s <= tt ? f * qk[i] : 0.0f;
+        e4[i] = __shfl(E, tt, 64);
+      }
+      wave_sync();
+      solve_chunk(ab, lane, T - tb, e4, um, om);
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        uint32_t hi, mid, lo;
+        split2(um[i], om[i], hi, mid, lo);
+        const int tt = 4 * quad + i;
+        ck.tm[0][tt][s] = static_cast<uint16_t>(hi);
+        ck.tm[1][tt][s] = static_cast<uint16_t>(mid);
+        ck.tm[2][tt][s] = static_cast<uint16_t>(lo);
+        ck.tm[0][16 + tt][s] = static_cast<uint16_t>(hi >> 16);
+        ck.tm[1][16 + tt][s] = static_cast<uint16_t>(mid >> 16);
+        ck.tm[2][16 + tt][s] = static_cast<uint16_t>(lo >> 16);
+      }
+    }
+  };
+
+  // ---- KDA staging by four waves in three steps, a barrier after each: waves
+  // 0 and 1 take the first eight tokens, waves 2 and 3 the others
+  float ka[2][4];  // the lane's decays
+  auto kda_operands = [&](typename P::Chunk& ck) __attribute__((always_inline)) {
+    if constexpr (KDA) {
+      const int half = wave >> 1;
+      const int lane = lane_now(), ph = lane >> 5, l32 = lane & 31;
+      // cum[i]: the channel's product between token 7 and token i of the lane's four
+      float cum[2][4];
+      float(&a)[2][4] = ka;
+      uint32_t bad = 0u;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        a[0][i] = __expf(bf16_lo(in.gp[i]));
+        a[1][i] = __expf(bf16_hi(in.gp[i]));
+        bad |= nonfinite(in.kp[i]) | nonfinite(in.qp[i]);
+      }
+      float whole[2];
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        const float mine = (a[m][0] * a[m][1]) * (a[m][2] * a[m][3]);
+        const float other = __shfl_xor(mine, 32, 64);
+        float run = (half == 0) == (ph == 0) ? other : 1.0f;  // the four tokens nearer to token 7
+        if (half == 0) {
+#pragma unroll
+          for (int i = 3; i >= 0; --i) {
+            cum[m][i] = run;
+            run *= a[m][i];
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            run *= a[m][i];
+            cum[m][i] = run;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (!(cum[m][i] >= kRhoMin && cum[m][i] <= kRhoMax)) bad = 1u;
+        whole[m] = run;
+        if (!(run <= FLT_MAX)) bad = 1u;
+      }
+      const float beta = bf16_to_f32(static_cast<uint16_t>(in.beta));
+      if (!(fabsf(beta) <= FLT_MAX)) bad = 1u;
+      const bool any = __builtin_amdgcn_ballot_w64(bad != 0u) != 0;
+      if (lane == 0) ck.flag[wave] = any ? 1 : 0;
+      uint32_t vbad = 0u;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) vbad |= nonfinite(in.v[KDA ? e : 0]);
+      const bool v_flagged = __builtin_amdgcn_ballot_w64(vbad != 0u) != 0;
+      if (lane == 0) ck.vflag[wave] = v_flagged ? 1 : 0;
+      if (wave == 0 && lane < kC) ck.beta[lane] = beta;
+      // the lanes of a channel's far tokens hold the product of all eight
+      if ((half == 0) == (ph == 0))
+        *reinterpret_cast<float2*>(&(half == 0 ? ck.pre : ck.fin)[64 * (wave & 1) + 2 * l32]) =
+            make_float2(whole[0], whole[1]);
+      // row 8 half + 4 ph + i: (at ^ 16 i) + i rows; q 16 rows after k
+      const int first = 8 * half + 4 * ph;
+      const int at = row_at(first, 8 * (wave & 1) + (l32 >> 2)) + 4 * (l32 & 3);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = (at ^ (i << 4)) + i * kRow;
+        const float i0 = refined_rcp(cum[0][i]), i1 = refined_rcp(cum[1][i]);
+        const float f0 = half == 0 ? i0 : cum[0][i], f1 = half == 0 ? i1 : cum[1][i];
+        const float n0 = half == 0 ? cum[0][i] : i0, n1 = half == 0 ? cum[1][i] : i1;
+        const float k0 = bf16_lo(in.kp[i]), k1 = bf16_hi(in.kp[i]);
+        uint32_t s3[3];
+        split2(k0 * f0, k1 * f1, s3[0], s3[1], s3[2]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+          *reinterpret_cast<uint32_t*>(ck.kq[KDA ? j : 0] + row) = s3[j];
+        split2(bf16_lo(in.qp[i]) * f0, bf16_hi(in.qp[i]) * f1, s3[0], s3[1], s3[2]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+          *reinterpret_cast<uint32_t*>(ck.kq[KDA ? j : 0] + row + 16 * kRow) = s3[j];
+        split2(k0 * n0, k1 * n1, s3[0], s3[1], s3[2]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) *reinterpret_cast<uint32_t*>(ck.kh[j] + row) = s3[j];
+      }
+    }
+  };
+  // one wave of each half of the rows: A = beta_s k~_t.k^_s, B = beta_s q~_t.k^_s;
+  // for a flagged chunk k, q and the decays themselves instead
+  auto kda_products = [&](typename P::Chunk& ck, int who) __attribute__((always_inline)) {
+    if constexpr (KDA) {
+      const int lane = lane_now();
+      if (__builtin_expect(flagged(ck), 0)) {
+        const int half = wave >> 1, ph = lane >> 5, l32 = lane & 31, first = 8 * half + 4 * ph;
+        const int at = row_at(first, 8 * (wave & 1) + (l32 >> 2)) + 4 * (l32 & 3);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uint8_t* row = ck.kq[0] + (at ^ (i << 4)) + i * kRow;
+          *reinterpret_cast<uint32_t*>(row) = in.kp[i];
+          *reinterpret_cast<uint32_t*>(row + 16 * kRow) = in.qp[i];
+          reinterpret_cast<float2*>(ck.kq[NA > 1 ? 1 : 0])[(first + i) * (kD / 2) + 32 * (wave & 1) +
+                                                           l32] = make_float2(ka[0][i], ka[1][i]);
+        }
+        return;
+      }
+      if (((wave ^ who) & 2) != 0) return;
+      const int s = lane & 15, quad = lane >> 4, rows = (wave ^ who) & 1;
+      f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
+      const int at_b = row_at(s, quad), at_a = at_b + 16 * rows * kRow;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        u4v fa[3], fb[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          fa[j] = *reinterpret_cast<const u4v*>(ck.kq[KDA ? j : 0] + (at_a ^ (ks << 6)));
+          fb[j] = *reinterpret_cast<const u4v*>(ck.kh[j] + (at_b ^ (ks << 6)));
+        }
+        acc = mfma16(fa[2], fb[0], acc);
+        acc = mfma16(fa[0], fb[2], acc);
+        acc = mfma16(fa[1], fb[1], acc);
+        acc = mfma16(fa[1], fb[0], acc);
+        acc = mfma16(fa[0], fb[1], acc);
+        acc = mfma16(fa[0], fb[0], acc);
+      }
+      const float bs = ck.beta[s];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int tt = 4 * quad + i;
+        const bool in_tri = rows == 0 ? s < tt : s <= tt;
+        ck.tm[16 * rows + tt][s] = in_tri ? bs * acc[i] : 0.0f;
+      }
+    }
+  };
+  auto kda_solve = [&](typename P::Chunk& ck, int tb, int who) __attribute__((always_inline)) {
+    if constexpr (KDA) {
+      if (wave != who || flagged(ck)) return;
+      const int lane = lane_now(), s = lane & 15, quad = lane >> 4;
+      float e4[4], um[4], om[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) e4[i] = ck.beta[4 * quad + i];
+      solve_chunk(ck.tm, lane, T - tb, e4, um, om);
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        ck.tm[4 * quad + i][s] = um[i];
+        ck.tm[16 + 4 * quad + i][s] = om[i];
+      }
+    }
+  };
+
+  auto stage = [&](typename P::Chunk* buf, int tb0) __attribute__((always_inline)) {
+    load_inputs(tb0);
+    if constexpr (!KDA) stage_gdn(buf[wave], tb0 + kC * wave);
+  };
+  constexpr int kStep = NC * kC;
   uint32_t seen0, seen1;
   touch(0, seen0, seen1);
+  // ---- SPLIT: the staging waves. They meet every barrier of the others: four
+  // while the tile passes through LDS, those of the chunks, and those of the
+  // way out
+  if (stages) {
+    auto staged = [&](int tb0) __attribute__((always_inline)) {
+      typename P::Chunk* buf = L + (tb0 / kStep & 1) * NC;
+      if (tb0 < T) {
+        asm volatile("" ::"v"(seen0), "v"(seen1));
+        stage(buf, tb0);
+        if (tb0 + kStep < T) touch(tb0 + kStep, seen0, seen1);
+      }
+      if constexpr (KDA) {
+        const int who = (tb0 / kC + h) & 3;
+        if (tb0 < T) kda_operands(buf[0]);
+        __syncthreads();
+        if (tb0 < T) kda_products(buf[0], who);
+        __syncthreads();
+        if (tb0 < T) kda_solve(buf[0], tb0, who);
+        __syncthreads();
+      }
+    };
+    staged(0);
+    for (int i = 0; i < (KDA ? 1 : 4); ++i) __syncthreads();
+#pragma unroll 1
+    for (int tb0 = 0; tb0 < T; tb0 += kStep) {
+      if constexpr (!KDA) __syncthreads();
+      staged(tb0 + kStep);
+    }
+    for (int i = 0; i < (KIND == kNvfp4 ? 6 : 4); ++i) __syncthreads();
+    return;
+  }
 
   // ---- the tile, row slices through LDS into natural channel order: thread
   // t moves columns 16 cg .. + 15 of tile rows t / 8 + 32 i
@@ -446,12 +724,9 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
     }
   }
 
-  // the lane id, formed anew in each phase (see opaque)
-  auto lane_now = [&]() { return opaque(t) & 63; };
-
   // ---- one flagged chunk token by token in fp32 (n tokens from token tb):
   // rows of k and q in bf16 from LDS; KDA's decays in fp32 from LDS
-  auto run_tokens = [&](const typename P::Chunk& ck, int tb, int n) {
+  auto run_tokens = [&](const typename P::Chunk& ck, int tb, int n) __attribute__((always_inline)) {
     const uint8_t* kq = ck.kq[0];
     const int lane = lane_now(), ph = lane >> 5, col = 32 * wave + (lane & 31);
 #pragma unroll 1
@@ -508,230 +783,11 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
   };
 
 
-  auto chunk_flag = [&](int c) -> bool {
-    if constexpr (KDA)
-      return (L[c].flag[0] | L[c].flag[1] | L[c].flag[2] | L[c].flag[3] | L[c].vflag[0] |
-              L[c].vflag[1] | L[c].vflag[2] | L[c].vflag[3]) != 0;
-    else
-      return L[c].flag != 0;
-  };
-
-  // ---- GDN staging, wave-local: wave w stages chunk w
-  auto stage_gdn = [&](int tb) {
-    if constexpr (!KDA) {
-      if (tb >= T) return;
-      typename P::Chunk& ck = L[wave];
-      const int lane = lane_now();
-      uint32_t bad = 0u;
-#pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        const int row = (lane >> 4) + 4 * i;
-        *reinterpret_cast<u4v*>(ck.kq[0] + row_at(row, lane & 15)) = in.k[i];
-        *reinterpret_cast<u4v*>(ck.kq[0] + row_at(16 + row, lane & 15)) = in.q[i];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          bad |= nonfinite(in.k[i][j]) | nonfinite(in.q[i][j]);
-      }
-      const float a = __expf(bf16_to_f32(static_cast<uint16_t>(in.g)));  // 1 past the end
-      const float beta = bf16_to_f32(static_cast<uint16_t>(in.beta));
-      if (!(a <= FLT_MAX) || !(fabsf(beta) <= FLT_MAX)) bad = 1u;
-      const bool flagged = __builtin_amdgcn_ballot_w64(bad != 0u) != 0;
-      if (lane == 0) ck.flag = flagged ? 1 : 0;
-      if (lane < kC) {
-        ck.a[lane] = a;
-        ck.beta[lane] = beta;
-      }
-      if (flagged) return;
-      // decay ratios: this lane's column s, rows t = 4 quad + i
-      const int s = lane & 15, quad = lane >> 4;
-      float Lr[4] = {0.0f, 0.0f, 0.0f, 0.0f}, G = 1.0f, run = 1.0f, Gs = 1.0f;
-#pragma unroll
-      for (int tt = 0; tt < kC; ++tt) {
-        const float at = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), tt));
-        G *= at;
-        if (s == tt) Gs = G;
-        run = tt <= s ? 1.0f : run * at;
-        if (quad == (tt >> 2)) Lr[tt & 3] = run;
-      }
-      if (lane < kC) ck.G[lane] = Gs;
-      const float E = run * beta;  // L_{15,s} beta_s
-      wave_sync();
-      f4v kk = {0.0f, 0.0f, 0.0f, 0.0f}, qk = kk;
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const u4v fk = *reinterpret_cast<const u4v*>(ck.kq[0] + row_at(s, 4 * ks + quad));
-        const u4v fq = *reinterpret_cast<const u4v*>(ck.kq[0] + row_at(16 + s, 4 * ks + quad));
-        kk = mfma16(fk, fk, kk);
-        qk = mfma16(fq, fk, qk);
-      }
-      float(*ab)[kC] = reinterpret_cast<float(*)[kC]>(ck.tm);
-      float e4[4], um[4], om[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int tt = 4 * quad + i;
-        const float f = Lr[i] * beta;
-        ab[tt][s] = s < tt ? f * kk[i] : 0.0f;
-        ab[16 + tt][s] = s <= tt ? f * qk[i] : 0.0f;
-        e4[i] = __shfl(E, tt, 64);
-      }
-      wave_sync();
-      solve_chunk(ab, lane, T - tb, e4, um, om);
-      wave_sync();
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        uint32_t hi, mid, lo;
-        split2(um[i], om[i], hi, mid, lo);
-        const int tt = 4 * quad + i;
-        ck.tm[0][tt][s] = static_cast<uint16_t>(hi);
-        ck.tm[1][tt][s] = static_cast<uint16_t>(mid);
-        ck.tm[2][tt][s] = static_cast<uint16_t>(lo);
-        ck.tm[0][16 + tt][s] = static_cast<uint16_t>(hi >> 16);
-        ck.tm[1][16 + tt][s] = static_cast<uint16_t>(mid >> 16);
-        ck.tm[2][16 + tt][s] = static_cast<uint16_t>(lo >> 16);
-      }
-    }
-  };
-
-  // ---- KDA staging by the whole workgroup: waves 0 and 1 take the first
-  // eight tokens, waves 2 and 3 the others
-  auto stage_kda = [&](int tb, int who) {
-    if constexpr (KDA) {
-      const int half = wave >> 1;
-      const int lane = lane_now(), ph = lane >> 5, l32 = lane & 31;
-      typename P::Chunk& ck = L[0];
-      // cum[i]: the channel's product between token 7 and token i of the lane's four
-      float a[2][4], cum[2][4];
-      uint32_t bad = 0u;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[0][i] = __expf(bf16_lo(in.gp[i]));
-        a[1][i] = __expf(bf16_hi(in.gp[i]));
-        bad |= nonfinite(in.kp[i]) | nonfinite(in.qp[i]);
-      }
-      float whole[2];
-#pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        const float mine = (a[m][0] * a[m][1]) * (a[m][2] * a[m][3]);
-        const float other = __shfl_xor(mine, 32, 64);
-        float run = (half == 0) == (ph == 0) ? other : 1.0f;  // the four tokens nearer to token 7
-        if (half == 0) {
-#pragma unroll
-          for (int i = 3; i >= 0; --i) {
-            cum[m][i] = run;
-            run *= a[m][i];
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            run *= a[m][i];
-            cum[m][i] = run;
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (!(cum[m][i] >= kRhoMin && cum[m][i] <= kRhoMax)) bad = 1u;
-        whole[m] = run;
-        if (!(run <= FLT_MAX)) bad = 1u;
-      }
-      const float beta = bf16_to_f32(static_cast<uint16_t>(in.beta));
-      if (!(fabsf(beta) <= FLT_MAX)) bad = 1u;
-      const bool flagged = __builtin_amdgcn_ballot_w64(bad != 0u) != 0;
-      if (lane == 0) ck.flag[wave] = flagged ? 1 : 0;
-      uint32_t vbad = 0u;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) vbad |= nonfinite(in.v[KDA ? e : 0]);
-      const bool v_flagged = __builtin_amdgcn_ballot_w64(vbad != 0u) != 0;
-      if (lane == 0) ck.vflag[wave] = v_flagged ? 1 : 0;
-      if (wave == 0 && lane < kC) ck.beta[lane] = beta;
-      // the lanes of a channel's far tokens hold the product of all eight
-      if ((half == 0) == (ph == 0))
-        *reinterpret_cast<float2*>(&(half == 0 ? ck.pre : ck.fin)[64 * (wave & 1) + 2 * l32]) =
-            make_float2(whole[0], whole[1]);
-      // row 8 half + 4 ph + i: (at ^ 16 i) + i rows; q 16 rows after k
-      const int first = 8 * half + 4 * ph;
-      const int at = row_at(first, 8 * (wave & 1) + (l32 >> 2)) + 4 * (l32 & 3);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = (at ^ (i << 4)) + i * kRow;
-        const float i0 = refined_rcp(cum[0][i]), i1 = refined_rcp(cum[1][i]);
-        const float f0 = half == 0 ? i0 : cum[0][i], f1 = half == 0 ? i1 : cum[1][i];
-        const float n0 = half == 0 ? cum[0][i] : i0, n1 = half == 0 ? cum[1][i] : i1;
-        const float k0 = bf16_lo(in.kp[i]), k1 = bf16_hi(in.kp[i]);
-        uint32_t s3[3];
-        split2(k0 * f0, k1 * f1, s3[0], s3[1], s3[2]);
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-          *reinterpret_cast<uint32_t*>(ck.kq[KDA ? j : 0] + row) = s3[j];
-        split2(bf16_lo(in.qp[i]) * f0, bf16_hi(in.qp[i]) * f1, s3[0], s3[1], s3[2]);
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-          *reinterpret_cast<uint32_t*>(ck.kq[KDA ? j : 0] + row + 16 * kRow) = s3[j];
-        split2(k0 * n0, k1 * n1, s3[0], s3[1], s3[2]);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) *reinterpret_cast<uint32_t*>(ck.kh[j] + row) = s3[j];
-      }
-      __syncthreads();
-      const bool slow = __builtin_amdgcn_readfirstlane(chunk_flag(0) ? 1 : 0) != 0;
-      if (__builtin_expect(slow, 0)) {  // k, q and the decays themselves instead
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          uint8_t* row = ck.kq[0] + (at ^ (i << 4)) + i * kRow;
-          *reinterpret_cast<uint32_t*>(row) = in.kp[i];
-          *reinterpret_cast<uint32_t*>(row + 16 * kRow) = in.qp[i];
-          reinterpret_cast<float2*>(ck.kq[NA > 1 ? 1 : 0])[(first + i) * (kD / 2) + 32 * (wave & 1) +
-                                                           l32] = make_float2(a[0][i], a[1][i]);
-        }
-        __syncthreads();
-        return;
-      }
-      // one wave of each half of the rows: A = beta_s k~_t.k^_s, B = beta_s q~_t.k^_s
-      const int s = lane & 15, quad = lane >> 4, rows = (wave ^ who) & 1;
-      if (((wave ^ who) & 2) == 0) {
-        f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        const int at_b = opaque(row_at(s, quad)), at_a = at_b + 16 * rows * kRow;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          u4v fa[3], fb[3];
-#pragma unroll
-          for (int j = 0; j < 3; ++j) {
-            fa[j] = *reinterpret_cast<const u4v*>(ck.kq[KDA ? j : 0] + (at_a ^ (ks << 6)));
-            fb[j] = *reinterpret_cast<const u4v*>(ck.kh[j] + (at_b ^ (ks << 6)));
-          }
-          acc = mfma16(fa[2], fb[0], acc);
-          acc = mfma16(fa[0], fb[2], acc);
-          acc = mfma16(fa[1], fb[1], acc);
-          acc = mfma16(fa[1], fb[0], acc);
-          acc = mfma16(fa[0], fb[1], acc);
-          acc = mfma16(fa[0], fb[0], acc);
-        }
-        const float bs = ck.beta[s];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int tt = 4 * quad + i;
-          const bool in_tri = rows == 0 ? s < tt : s <= tt;
-          ck.tm[16 * rows + tt][s] = in_tri ? bs * acc[i] : 0.0f;
-        }
-      }
-      __syncthreads();
-      if (wave == who) {  // the others start on the chunk; they meet where it needs tm
-        float e4[4], um[4], om[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) e4[i] = ck.beta[4 * quad + i];
-        solve_chunk(ck.tm, lane, T - tb, e4, um, om);
-        wave_sync();
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          ck.tm[4 * quad + i][s] = um[i];
-          ck.tm[16 + 4 * quad + i][s] = om[i];
-        }
-      }
-    }
-  };
-
   // ---- one chunk of up to 16 tokens from token tb on this wave's columns
   // (vr: v of tokens 8 ph + e, this lane's column); false, and nothing done, if
   // that v is not finite (GDN; KDA's flags have it)
-  auto run_chunk = [&](const typename P::Chunk& ck, int tb, const uint32_t (&vr)[8]) -> bool {
+  auto run_chunk = [&](const typename P::Chunk& ck, int tb,
+                       const uint32_t (&vr)[8]) __attribute__((always_inline)) -> bool {
     const int lane = lane_now(), ph = lane >> 5, l32 = lane & 31, col = 32 * wave + l32;
     // rows of the left-hand operands: lane l32 is row m of the 32; m % 16 bits
     // (r, p, i) stand for token (p, r, i), so that a lane's accumulators 0..7
@@ -762,7 +818,7 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
     const int a_at = row_at(m_row, ph);  // piece 2 ks + ph: bits 5 and up xor 2 ks
     Split8 sb;
     u4v fa[NA];
-    auto step_operands = [&](int ks) {
+    auto step_operands = [&](int ks) __attribute__((always_inline)) {
       float x[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = S[ks >> 1][8 * (ks & 1) + e];
@@ -778,7 +834,7 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
       // the operands of one step (GDN: two) at a time: registers
       if (KDA || (ks & 1)) __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (KDA) __syncthreads();  // tm is there
+    if constexpr (KDA) __syncthreads();  // tm is there (SPLIT: the other waves' first step is done)
     if constexpr (!KDA) {
       uint32_t bad = 0u;
 #pragma unroll
@@ -839,6 +895,7 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
                                                 at + e * step, 0, 0);
       }
     }
+    if constexpr (KDA && SPLIT) __syncthreads();
     // S = G_C S0 + K^T U
     float U[8];
 #pragma unroll
@@ -887,7 +944,7 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
     return true;
   };
 
-  auto load_v = [&](int tb, uint32_t (&vr)[8]) {
+  auto load_v = [&](int tb, uint32_t (&vr)[8]) __attribute__((always_inline)) {
     const auto rv = rows_rsrc(p.v + ((tok0 + tb) * p.HV + h) * kD, v_step, kRow,
                               T - tb < kC ? T - tb : kC);
     const int lane = lane_now(), v_at = 8 * (lane >> 5) * v_step + 2 * (32 * wave + (lane & 31));
@@ -895,30 +952,54 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
     for (int e = 0; e < 8; ++e)
       vr[e] = __builtin_amdgcn_raw_buffer_load_b16(rv, e * v_step + v_at, 0, 0);
   };
-#pragma unroll 1
-  for (int tb0 = 0; tb0 < T; tb0 += NC * kC) {
-    asm volatile("" ::"v"(seen0), "v"(seen1));
-    load_inputs(tb0);
-    uint32_t vr[8];
-    if constexpr (KDA) {
-      stage_kda(tb0, (tb0 / kC + h) & 3);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) vr[e] = in.v[KDA ? e : 0];
-    } else {
-      stage_gdn(tb0 + kC * wave);
-      __syncthreads();
-    }
-    if (tb0 + NC * kC < T) touch(tb0 + NC * kC, seen0, seen1);
+  auto run = [&](const typename P::Chunk* buf, int tb0) __attribute__((always_inline)) {
 #pragma unroll 1
     for (int c = 0; c < NC && tb0 + kC * c < T; ++c) {
-      const int tb = tb0 + kC * c;
-      bool slow = chunk_flag(c);
-      if constexpr (!KDA) load_v(tb, vr);
-      if (!__builtin_amdgcn_readfirstlane(slow ? 1 : 0)) slow = !run_chunk(L[c], tb, vr);
-      if (__builtin_expect(__builtin_amdgcn_readfirstlane(slow ? 1 : 0), 0))
-        run_tokens(L[c], tb, T - tb < kC ? T - tb : kC);
+      const int tb = tb0 + kC * c, n = T - tb < kC ? T - tb : kC;
+      uint32_t vr[8];
+      if constexpr (KDA && !SPLIT) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) vr[e] = in.v[KDA ? e : 0];
+      } else {
+        load_v(tb, vr);
+      }
+      bool done = false;
+      if (!flagged(buf[c])) done = run_chunk(buf[c], tb, vr);
+      if (__builtin_expect(!__builtin_amdgcn_readfirstlane(done ? 1 : 0), 0)) {
+        run_tokens(buf[c], tb, n);
+        if constexpr (KDA && SPLIT) {  // those of run_chunk
+          __syncthreads();
+          __syncthreads();
+        }
+      }
     }
-    __syncthreads();
+  };
+  if constexpr (!SPLIT) {
+#pragma unroll 1
+    for (int tb0 = 0; tb0 < T; tb0 += kStep) {
+      asm volatile("" ::"v"(seen0), "v"(seen1));
+      stage(L, tb0);
+      if constexpr (KDA) {
+        const int who = (tb0 / kC + h) & 3;
+        kda_operands(L[0]);
+        __syncthreads();
+        kda_products(L[0], who);
+        __syncthreads();
+        kda_solve(L[0], tb0, who);  // the other waves start on the chunk
+      } else {
+        __syncthreads();
+      }
+      if (tb0 + kStep < T) touch(tb0 + kStep, seen0, seen1);
+      run(L, tb0);
+      __syncthreads();
+    }
+  } else {
+#pragma unroll 1
+    for (int tb0 = 0; tb0 < T; tb0 += kStep) {
+      if constexpr (!KDA) __syncthreads();  // staged
+      run(L + (tb0 / kStep & 1) * NC, tb0);
+      if constexpr (KDA) __syncthreads();
+    }
   }
 
   // ---- store the final state per its tier, as it came
@@ -966,13 +1047,28 @@ __global__ __launch_bounds__(256, 3) void prefill_chunk128(const PrefillParams p
                                    s_g);
 }
 
+// A CU holds one eight-wave workgroup or three of four waves. While every tile
+// has a CU to itself, a wave's own instruction rate is what counts (one in 5
+// cycles, whatever else the CU could do), so staging beside the chunks pays;
+// with more tiles the second round it costs does not. One to eight requests of
+// 32 heads (up to 256 tiles), 1024 tokens: GDN 181-186 -> 135-137 us, KDA
+// 402-404 -> 280-283; 8 tokens: 10.3-11.4 -> 10.3-10.5 and 12.2-13.3 -> 11.4-12.5
+// (the first chunks are staged while the tile arrives). Twelve requests (384
+// tiles), 250 tokens: GDN 71 -> 84, KDA 136 -> 152.
+bool split_waves(int64_t tiles) { return tiles <= 256; }
+
+template <int KIND, bool KDA>
+void launch_kind(const PrefillParams& p, int B, hipStream_t stream) {
+  const dim3 grid(p.HV, B);
+  if (split_waves(static_cast<int64_t>(B) * p.HV))
+    hipLaunchKernelGGL((prefill_chunk128<KIND, KDA, true>), grid, dim3(512), 0, stream, p);
+  else
+    hipLaunchKernelGGL((prefill_chunk128<KIND, KDA, false>), grid, dim3(256), 0, stream, p);
+}
 template <int KIND>
 void launch_kind(bool kda, const PrefillParams& p, int B, hipStream_t stream) {
-  const dim3 grid(p.HV, B), block(256);
-  if (kda)
-    hipLaunchKernelGGL((prefill_chunk128<KIND, true>), grid, block, 0, stream, p);
-  else
-    hipLaunchKernelGGL((prefill_chunk128<KIND, false>), grid, block, 0, stream, p);
+  if (kda) launch_kind<KIND, true>(p, B, stream);
+  else launch_kind<KIND, false>(p, B, stream);
 }
 
 }  // namespace

@@ -190,14 +190,16 @@ def test_calibrate_sequence_gdn_vanishing_decay():
     np.testing.assert_allclose(sums[1], cal_ref.sums[0, 1], rtol=1e-5)
 
 
+@pytest.mark.parametrize("B", [2, 129])
 @pytest.mark.parametrize("kda", [False, True])
 @pytest.mark.parametrize("T", [1, 4, 5, 15, 16, 17, 33, 64, 65, 130])
-def test_prefill_chunk_edges(kda, T):
+def test_prefill_chunk_edges(kda, T, B):
     """d = 128 runs in chunks of 16 tokens, several staged together: one token,
     the edges of the four-row groups, of a chunk and of a staging block, and a
-    partial last chunk. FP32 state, so o and the state carry fp32 rounding
-    only (the bar of the FP32 path)."""
-    d, HK, HV, B = 128, 2 if kda else 1, 2, 2
+    partial last chunk; with up to 256 tiles staged by waves of their own, with
+    more (B = 129, two heads) by the waves that run them. FP32 state, so o and
+    the state carry fp32 rounding only (the bar of the FP32 path)."""
+    d, HK, HV = 128, 2 if kda else 1, 2
     seed = 760 + T
     slots = inputs.slot_order(seed, B + 1, B)
     perm = inputs.random_perms(seed, HV, d)
@@ -240,18 +242,19 @@ def test_prefill_inputs_at_odd_addresses(kda):
 
 
 @pytest.mark.parametrize("kda", [False, True])
+@pytest.mark.parametrize("B", [1, 258])
 @pytest.mark.parametrize("what", ["v", "k", "q"])
-def test_prefill_nonfinite_input_leaves_earlier_tokens(kda, what):
+def test_prefill_nonfinite_input_leaves_earlier_tokens(kda, what, B):
     """An infinite input value at one token: every earlier token's output, and
     for v and q everything the recurrence does not reach (other columns;
     later tokens and the state), is what it is without it."""
-    d, HK, HV, B, T, at = 128, 1, 1, 1, 40, 21
+    d, HK, HV, T, at = 128, 1, 1, 40, 21
     seed = 795
     ref = orc.Pool(orc.KIND_FP32, d, d, 0, 1, B, HV)
     orc.pack(ref, 0, np.arange(B), inputs.synthetic_states(seed, B, HV, d))
     inp = inputs.as_prefill(inputs.decode_inputs(seed, T, B, HK, HV, d, kda=kda))
     fn = D.damp_state_prefill_kda if kda else D.damp_state_prefill_gdn
-    res = []
+    res = []  # of request 0
     for bad in (False, True):
         x = {n: a.copy() for n, a in inp.items()}
         if bad:
@@ -272,3 +275,30 @@ def test_prefill_nonfinite_input_leaves_earlier_tokens(kda, what):
     if what == "q":
         keep = np.arange(T) != at
         assert rel_l2(o1[keep], o0[keep]) <= 1e-5 and rel_l2(s1, s0) <= 1e-5
+
+
+@pytest.mark.parametrize("kda", [False, True])
+def test_prefill_vanishing_decays_with_many_tiles(kda):
+    """Zero decays and decays whose products leave the range of the chunk form,
+    in a batch of more than 256 tiles: single-token chunks between chunks in
+    matrix form, every request against the oracle."""
+    d, HK, HV, B, T = 128, 1, 1, 260, 50
+    seed = 797
+    ref = orc.Pool(orc.KIND_FP32, d, d, 0, 1, B, HV)
+    orc.pack(ref, 0, np.arange(B), inputs.synthetic_states(seed, B, HV, d))
+    gpool = gpu_pool_from(ref, D)
+    inp = inputs.as_prefill(inputs.decode_inputs(seed, T, B, HK, HV, d, kda=kda))
+    g = inp["g"].copy()
+    bits = lambda x: inputs.to_bf16_bits(np.float32(x))[0]
+    g[0::3, 20] = bits(-np.inf)
+    if kda:
+        g[1::3, 17:30, 0, 9] = bits(-20.0)
+        g[2::3, 40:, 0, 100] = bits(-90.0)
+    else:
+        g[1::3, 17:30] = bits(-20.0)
+        g[2::3, 40:] = bits(-90.0)
+    inp["g"] = g
+    o_gpu, o_ref = _run(kda, ref, gpool, np.arange(B), inp, None)
+    state = gpool.buffer.cpu().numpy().view(np.float32)
+    assert np.isfinite(o_gpu).all() and np.isfinite(state).all()
+    assert rel_l2(o_gpu, o_ref) <= 1e-5 and rel_l2(state, ref.buf.view(np.float32)) <= 1e-5
