@@ -52,12 +52,35 @@ __global__ __launch_bounds__(NT) void update_kernel(const UpdateParams p) {
   const int cg = t % TPR, rg = t / TPR, col0 = cg * CPT;
   const size_t bh = static_cast<size_t>(b) * p.HV + h;
 
+  // ---- operands in tile-row order (gathered through the permutation), loaded
+  // before the slot id is looked at: neither waits for the other, and a small
+  // batch is as long as its chain of dependent loads
   const int slot = p.slot_idx[b];
+  const int hk = h / (p.HV / p.HK);
+  const uint16_t* kb = p.k + (static_cast<size_t>(b) * p.HK + hk) * D;
+  const uint16_t* qb = p.q + (static_cast<size_t>(b) * p.HK + hk) * D;
+  uint16_t kw[RPT], qw[RPT], gw[RPT];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int r = rg + RG * i;
+    const int u = p.perm ? (static_cast<int>(p.perm[static_cast<size_t>(h) * D + r]) & (D - 1)) : r;
+    kw[i] = kb[u];
+    qw[i] = qb[u];
+    gw[i] = KDA ? p.g[bh * D + u] : p.g[bh];
+  }
+  const uint16_t beta_w = p.beta[bh];
+  const uint16_t v_w = t < D ? p.v[bh * D + t] : 0;
+  uint16_t kn[(D + 63) / 64], qn[(D + 63) / 64];  // natural order, for q~ . k~
+#pragma unroll
+  for (int m = 0; m < (D + 63) / 64; ++m) {
+    kn[m] = lane + 64 * m < D ? kb[lane + 64 * m] : 0;
+    qn[m] = lane + 64 * m < D ? qb[lane + 64 * m] : 0;
+  }
+
   if (slot < 0 || slot >= p.num_slots) {  // padded request: o = 0, state untouched
     for (int j = t; j < D; j += NT) write_o(p, bh * D + j, 0.0f);
     return;
   }
-
   uint8_t* tile = p.layer_base + static_cast<size_t>(slot) * p.slot_stride +
                   static_cast<size_t>(h) * p.tile_stride;
   const int k_hi = KIND == kFp32 ? D : p.k_hi;
@@ -89,25 +112,22 @@ __global__ __launch_bounds__(NT) void update_kernel(const UpdateParams p) {
     }
   }
 
-  // ---- operands in tile-row order (gathered through the permutation) ------
-  const int hk = h / (p.HV / p.HK);
-  const uint16_t* kb = p.k + (static_cast<size_t>(b) * p.HK + hk) * D;
-  const uint16_t* qb = p.q + (static_cast<size_t>(b) * p.HK + hk) * D;
-  const float beta = bf16_to_f32(p.beta[bh]);
-  float alpha = 1.0f;
-  if (!KDA) alpha = expf(bf16_to_f32(p.g[bh]));
+  const float beta = bf16_to_f32(beta_w);
   float kk[RPT], qq[RPT], aa[RPT];
+  {
+    const float alpha = KDA ? 1.0f : expf(bf16_to_f32(gw[0]));
 #pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    const int r = rg + RG * i;
-    const int u = p.perm ? (static_cast<int>(p.perm[static_cast<size_t>(h) * D + r]) & (D - 1)) : r;
-    kk[i] = bf16_to_f32(kb[u]);
-    qq[i] = bf16_to_f32(qb[u]);
-    aa[i] = KDA ? expf(bf16_to_f32(p.g[bh * D + u])) : alpha;
+    for (int i = 0; i < RPT; ++i) {
+      kk[i] = bf16_to_f32(kw[i]);
+      qq[i] = bf16_to_f32(qw[i]);
+      aa[i] = KDA ? expf(bf16_to_f32(gw[i])) : alpha;
+    }
   }
   // q~ . k~ is permutation invariant: natural order, reduced over the wave.
   float qk = 0.0f;
-  for (int e = lane; e < D; e += 64) qk = fmaf(bf16_to_f32(qb[e]), bf16_to_f32(kb[e]), qk);
+#pragma unroll
+  for (int m = 0; m < (D + 63) / 64; ++m)
+    qk = fmaf(bf16_to_f32(qn[m]), bf16_to_f32(kn[m]), qk);
   qk = wave_sum(qk);
 
   // ---- dequantize and decay: S_bar = Lambda S -----------------------------
@@ -187,7 +207,7 @@ __global__ __launch_bounds__(NT) void update_kernel(const UpdateParams p) {
     for (int g = 0; g < RG; ++g) acc[g & 3] += red[g][t];
     tot = (acc[0] + acc[1]) + (acc[2] + acc[3]);
   }
-  if (t < D) dsh[t] = bf16_to_f32(p.v[bh * D + t]) - tot;  // delta = v - S_bar^T k~
+  if (t < D) dsh[t] = bf16_to_f32(v_w) - tot;  // delta = v - S_bar^T k~
   __syncthreads();
   if (t >= D && t < 2 * D) {
     const int j = t - D;
