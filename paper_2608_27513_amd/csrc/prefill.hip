@@ -1,8 +1,8 @@
 // Prefill of one chunk of tokens per request into the packed pool (App. A.5,
 // prefill path; section 3.1 Eq. (1)): the entry points, the choice of kernel,
 // and the generic kernel. At d = 128 prefill_chunk.hip runs the recurrence on
-// the matrix cores; the generic kernel takes the smaller head sizes and inputs
-// at addresses that the other kernel's wider loads do not take.
+// the matrix cores; the generic kernel takes the smaller head sizes (and token
+// rows too long for that kernel's 32-bit offsets).
 //
 // In the generic kernel one workgroup owns one (request, value head) tile: it
 // decodes the stored state once into registers, runs the recurrence of
@@ -252,12 +252,9 @@ void prefill_window(bool kda, const damp_pool* pool, int32_t layer, const int32_
   p.k_hi = pool->layout.kind == DAMP_STATE_FP32 ? 0 : pool->layout.k_hi;
   p.o_bf16 = o_bf16 ? 1 : 0;
   p.had = pool->layout.hadamard;
-  // the chunked kernel loads rows of q, k and v 16 bytes at a time and KDA's
-  // decays 4 at a time; inputs at other addresses take the generic kernel
-  const uintptr_t at = reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k) |
-                       reinterpret_cast<uintptr_t>(v);
-  if (pool->layout.d_k == 128 && at % 16 == 0 &&
-      (!kda || reinterpret_cast<uintptr_t>(g) % 4 == 0)) {
+  // the chunked kernel addresses up to 64 rows of 256 bytes per head and token,
+  // from its own base, with 32-bit offsets
+  if (pool->layout.d_k == 128 && int64_t{64} * 256 * p.HV <= INT32_MAX) {
     launch_prefill_chunk128(layout_codec(&pool->layout), kda, p, B, stream);
     return;
   }

@@ -33,7 +33,6 @@ struct PrefillParams {
 };
 
 // The d = 128 kernel of prefill_chunk.hip for a layout codec (internal.hpp).
-// q, k and v must be 16-byte aligned, and KDA's g 4-byte aligned.
 void launch_prefill_chunk128(int codec, bool kda, const PrefillParams& p, int B,
                              hipStream_t stream);
 

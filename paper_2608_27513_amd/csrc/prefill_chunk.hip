@@ -58,8 +58,8 @@
 // 16: the products within a chunk and T grow with its square.
 // Measured against the token-by-token fp32 kernel before it (two FMAs per
 // value and token for the read-outs, one for the update), GDN, B = 256, 32
-// heads, 64 tokens: 805 -> 319 us; KDA, B = 32, 250 tokens: 498 -> 265 us; GDN,
-// two requests of 1024 tokens: 728 -> 136 us; 2 tokens at B = 256: 154 -> 139 us
+// heads, 64 tokens: 805 -> 316 us; KDA, B = 32, 250 tokens: 498 -> 265 us; GDN,
+// two requests of 1024 tokens: 728 -> 134 us; 2 tokens at B = 256: 154 -> 139 us
 // (GDN), 167 -> 164 us (KDA).
 #include <cfloat>
 #include <cstdint>
@@ -359,6 +359,15 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
     uint32_t g, beta;
   } in;
   const int kq_step = p.HK * kRow, v_step = p.HV * kRow;
+  // buffer loads of a word and more need a word's alignment: k, q and KDA's g
+  // that do not have it are read by halves
+  const bool by_halves = ((reinterpret_cast<uintptr_t>(p.k) | reinterpret_cast<uintptr_t>(p.q) |
+                           (KDA ? reinterpret_cast<uintptr_t>(p.g) : 0)) & 2) != 0;
+  auto load_halves = [&](const auto& rsrc, int at) __attribute__((always_inline)) -> uint32_t {
+    const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(rsrc, at, 0, 0);
+    const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(rsrc, at + 2, 0, 0);
+    return lo | hi << 16;
+  };
   auto load_inputs = [&](int tb0) __attribute__((always_inline)) {
     const int lane = opaque(t) & 63, ph = lane >> 5, l32 = lane & 31, col = 32 * wave + l32;
     const int ntok = T - tb0 < NC * kC ? T - tb0 : NC * kC;
@@ -372,6 +381,14 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
 #pragma unroll
       for (int i = 0; i < NL; ++i) {
         const int kq = (tt + 4 * i) * kq_step + 16 * (lane & 15);
+        if (__builtin_expect(by_halves, 0)) {
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            in.k[i][w] = load_halves(rk, kq + 4 * w);
+            in.q[i][w] = load_halves(rq, kq + 4 * w);
+          }
+          continue;
+        }
         in.k[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, kq, 0, 0);
         in.q[i] = __builtin_amdgcn_raw_buffer_load_b128(rq, kq, 0, 0);
       }
@@ -385,6 +402,12 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
 #pragma unroll
       for (int i = 0; i < NL; ++i) {
         const int kq = (tt + i) * kq_step + at, gv = (tt + i) * v_step + at;
+        if (__builtin_expect(by_halves, 0)) {
+          in.kp[i] = load_halves(rk, kq);
+          in.qp[i] = load_halves(rq, kq);
+          in.gp[i] = load_halves(rg, gv);
+          continue;
+        }
         in.kp[i] = __builtin_amdgcn_raw_buffer_load_b32(rk, kq, 0, 0);
         in.qp[i] = __builtin_amdgcn_raw_buffer_load_b32(rq, kq, 0, 0);
         in.gp[i] = __builtin_amdgcn_raw_buffer_load_b32(rg, gv, 0, 0);
@@ -407,18 +430,18 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
     const auto rv = rows_rsrc(p.v + (row * p.HV + h) * kD, v_step, kRow, ntok);
     if constexpr (!KDA) {
       const int tt = (t >> 1) & 63, line = 128 * (t & 1);
-      x0 = t < 128 ? __builtin_amdgcn_raw_buffer_load_b32(rk, tt * kq_step + line, 0, 0)
-                   : __builtin_amdgcn_raw_buffer_load_b32(rq, tt * kq_step + line, 0, 0);
+      x0 = t < 128 ? __builtin_amdgcn_raw_buffer_load_b16(rk, tt * kq_step + line, 0, 0)
+                   : __builtin_amdgcn_raw_buffer_load_b16(rq, tt * kq_step + line, 0, 0);
       // v only ahead of the staging waves: before a whole round of chunks it
       // would be out of the L2 again when it is read
-      x1 = SPLIT && t < 128 ? __builtin_amdgcn_raw_buffer_load_b32(rv, tt * v_step + line, 0, 0) : 0u;
+      x1 = SPLIT && t < 128 ? __builtin_amdgcn_raw_buffer_load_b16(rv, tt * v_step + line, 0, 0) : 0u;
     } else {
       const auto rg = rows_rsrc(p.g + (row * p.HV + h) * kD, v_step, kRow, ntok);
       const int tt = (t >> 1) & 15, line = 128 * (t & 1);
-      x0 = wave == 0   ? __builtin_amdgcn_raw_buffer_load_b32(rk, tt * kq_step + line, 0, 0)
-           : wave == 1 ? __builtin_amdgcn_raw_buffer_load_b32(rq, tt * kq_step + line, 0, 0)
-           : wave == 2 ? __builtin_amdgcn_raw_buffer_load_b32(rv, tt * v_step + line, 0, 0)
-                       : __builtin_amdgcn_raw_buffer_load_b32(rg, tt * v_step + line, 0, 0);
+      x0 = wave == 0   ? __builtin_amdgcn_raw_buffer_load_b16(rk, tt * kq_step + line, 0, 0)
+           : wave == 1 ? __builtin_amdgcn_raw_buffer_load_b16(rq, tt * kq_step + line, 0, 0)
+           : wave == 2 ? __builtin_amdgcn_raw_buffer_load_b16(rv, tt * v_step + line, 0, 0)
+                       : __builtin_amdgcn_raw_buffer_load_b16(rg, tt * v_step + line, 0, 0);
       x1 = 0u;
     }
   };

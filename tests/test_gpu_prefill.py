@@ -215,30 +215,32 @@ def test_prefill_chunk_edges(kda, T, B):
 
 
 @pytest.mark.parametrize("kda", [False, True])
-def test_prefill_inputs_at_odd_addresses(kda):
-    """q, k, v (16 bytes) and KDA's g (4 bytes) at addresses the d = 128 kernel
-    does not take go through the generic kernel: the same outputs and state to
-    fp32 rounding."""
-    d, HK, HV, B, T = 128, 2, 2, 2, 21
+@pytest.mark.parametrize("B", [2, 129])
+def test_prefill_inputs_at_odd_addresses(kda, B):
+    """q, k, v and g 2 or 4 bytes off: the d = 128 kernel reads k, q and KDA's
+    g by halves where they are not word aligned, and 16 bytes at a time where
+    they are: the same outputs and state."""
+    d, HK, HV, T = 128, 2, 2, 21
     seed = 790
     ref = orc.Pool(orc.KIND_FP32, d, d, 0, 1, B, HV)
     orc.pack(ref, 0, np.arange(B), inputs.synthetic_states(seed, B, HV, d))
     inp = dev_inputs(inputs.as_prefill(inputs.decode_inputs(seed, T, B, HK, HV, d, kda=kda)))
     fn = D.damp_state_prefill_kda if kda else D.damp_state_prefill_gdn
 
-    def shifted(t):  # the same values, 2 bytes off
-        raw = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")
-        raw[1:] = t.reshape(-1)
-        return raw[1:].view(t.shape)
+    def shifted(t, by):  # the same values, 2 by bytes off
+        raw = torch.empty(t.numel() + by, dtype=t.dtype, device="cuda")
+        raw[by:] = t.reshape(-1)
+        return raw[by:].view(t.shape)
 
     got = []
-    for odd in ((), ("q",), ("k",), ("v",), ("q", "k", "v", "g", "beta")):
+    for odd, by in (((), 0), (("q",), 1), (("k",), 1), (("v",), 1), (("g",), 1),
+                    (("q", "k", "v", "g", "beta"), 1), (("q", "k", "v", "g", "beta"), 2)):
         pool = gpu_pool_from(ref, D)
-        a = {n: shifted(t) if n in odd else t for n, t in inp.items()}
+        a = {n: shifted(t, by) if n in odd else t for n, t in inp.items()}
         o = fn(pool, 0, dev_i32(np.arange(B)), a["q"], a["k"], a["v"], a["g"], a["beta"])
         got.append((o.cpu().numpy(), pool.buffer.cpu().numpy().view(np.float32)))
     for o, s in got[1:]:
-        assert rel_l2(o, got[0][0]) <= 1e-5 and rel_l2(s, got[0][1]) <= 1e-5
+        assert np.array_equal(o, got[0][0]) and np.array_equal(s, got[0][1])
 
 
 @pytest.mark.parametrize("kda", [False, True])
