@@ -45,7 +45,8 @@ PROFILED_SOURCES = {
     "update_stream128": KERNEL_SOURCES,
     "update_fp32_128": ["paper_2608_27513_amd/csrc/update_fp32.hip", "paper_2608_27513_amd/csrc/update.hpp",
                         "paper_2608_27513_amd/csrc/device.hpp"],
-    "prefill_blk128": ["paper_2608_27513_amd/csrc/prefill.hip", "paper_2608_27513_amd/csrc/device.hpp"],
+    "prefill_chunk128": ["paper_2608_27513_amd/csrc/prefill_chunk.hip", "paper_2608_27513_amd/csrc/prefill.hpp",
+                         "paper_2608_27513_amd/csrc/device.hpp"],
     "pack_unpack": ["paper_2608_27513_amd/csrc/pack.hip", "paper_2608_27513_amd/csrc/device.hpp"],
     "copy_inplace_nt": ["paper_2608_27513_amd/bench_csrc/copy_ceiling.hip"],
     "copy_tiles_nt": ["paper_2608_27513_amd/bench_csrc/copy_ceiling.hip"],
@@ -597,9 +598,10 @@ def prefill_bench(torch, D, inputs, steps: int, log=print, T: int = 64, kda: boo
     """Prefill of one T-token chunk per request (App. A.5, prefill path) on
     the B=256 GDN workload (16 key / 32 value heads, d=128, 16 BF16 rows) or
     the KDA one (32 heads, per-channel decay):
-    decode the stored state once, T fp32 steps, store once. Reports tokens per
-    second and the fp32 rate (7 flops per state value and token: decay, two
-    read-outs, the update), against the vector fp32 peak."""
+    decode the stored state once, T tokens, store once. Reports tokens per
+    second and the rate of the recurrence's flops (7 per state value and token:
+    decay, two read-outs, the update) against the vector fp32 peak, which the
+    matrix cores' split products may exceed."""
     B, HV, d, k_hi = 256, 32, 128, 16
     HK = HV if kda else 16
     gen = torch.Generator(device="cuda")
