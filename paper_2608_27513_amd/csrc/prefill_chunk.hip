@@ -20,6 +20,10 @@
 // and K^T U have one factor exact and take three products; a product of two
 // split factors takes the six whose weight is above 2^-26. Decay ratios are
 // running products as in the sequential form, never exponentials of sums.
+// A zero in a product does not hide a factor that is not finite, so a value out
+// of range at one token would reach the tokens before it: a chunk whose inputs,
+// decay products, T or B T are not all finite, and a wave whose R is not, run
+// token by token in fp32 (run_tokens).
 //
 // KDA's decay is per key channel, so k and q carry it: with the reference
 // token r = 7 of a chunk and rho_t the product of a channel's decays between
@@ -28,8 +32,8 @@
 // and, with S0' = diag(a_0 ... a_7) S0, the same formulas hold with L = G = 1:
 //   A_ts = beta_s k~_t.k^_s, S_C = diag(a_8 ... a_15) (S0' + K^^T U).
 // The eight-token products on either side of r must stay in [2^-96, 2^96];
-// a chunk where some channel leaves it (a zero decay included), or whose
-// inputs are not finite, runs token by token in fp32 (run_tokens).
+// a chunk where some channel leaves it (a zero decay included) runs token by
+// token too.
 //
 // Mapping. A workgroup of four waves owns one (request, value head) tile;
 // wave w holds columns 32 w .. 32 w + 31 of the state for all 128 channels, in
@@ -477,13 +481,10 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
       const float a = __expf(bf16_to_f32(static_cast<uint16_t>(in.g)));  // 1 past the end
       const float beta = bf16_to_f32(static_cast<uint16_t>(in.beta));
       if (!(a <= FLT_MAX) || !(fabsf(beta) <= FLT_MAX)) bad = 1u;
-      const bool any = __builtin_amdgcn_ballot_w64(bad != 0u) != 0;
-      if (lane == 0) ck.flag = any ? 1 : 0;
       if (lane < kC) {
         ck.a[lane] = a;
         ck.beta[lane] = beta;
       }
-      if (any) return;
       // decay ratios: this lane's column s, rows t = 4 quad + i
       const int s = lane & 15, quad = lane >> 4;
       float Lr[4] = {0.0f, 0.0f, 0.0f, 0.0f}, G = 1.0f, run = 1.0f, Gs = 1.0f;
@@ -497,6 +498,11 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
       }
       if (lane < kC) ck.G[lane] = Gs;
       const float E = run * beta;  // L_{15,s} beta_s
+      // an overflow of G or of a ratio is in the last one too
+      if (!(G <= FLT_MAX) || !(fabsf(E) <= FLT_MAX)) bad = 1u;
+      const bool any = __builtin_amdgcn_ballot_w64(bad != 0u) != 0;
+      if (lane == 0) ck.flag = any ? 1 : 0;
+      if (any) return;
       wave_sync();
       f4v kk = {0.0f, 0.0f, 0.0f, 0.0f}, qk = kk;
 #pragma unroll
@@ -518,6 +524,11 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
       }
       wave_sync();
       solve_chunk(ab, lane, T - tb, e4, um, om);
+      // keys that amplify the state out of range within the chunk
+      float sum = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum += fabsf(um[i]) + fabsf(om[i]);
+      if (__builtin_amdgcn_ballot_w64(!(sum <= FLT_MAX)) != 0 && lane == 0) ck.flag = 1;
       wave_sync();
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -822,7 +833,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
 
   // ---- one chunk of up to 16 tokens from token tb on this wave's columns
   // (vr: v of tokens 8 ph + e, this lane's column); false, and nothing done, if
-  // that v is not finite (GDN; KDA's flags have it)
+  // some R of this wave's columns is not finite (GDN; KDA's flags have v)
   auto run_chunk = [&](const typename P::Chunk& ck, int tb,
                        const uint32_t (&vr)[8]) __attribute__((always_inline)) -> bool {
     const int lane = lane_now(), ph = lane >> 5, l32 = lane & 31, col = 32 * wave + l32;
@@ -872,12 +883,6 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
       if (KDA || (ks & 1)) __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (KDA) __syncthreads();  // tm is there (SPLIT: the other waves' first step is done)
-    if constexpr (!KDA) {
-      uint32_t bad = 0u;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) bad |= nonfinite(vr[e]);
-      if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad != 0u) != 0, 0)) return false;
-    }
     // R = V - G K S0; G Q S0 stays in acc[8 + e]
     float R[8];
 #pragma unroll
@@ -908,6 +913,12 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
           tm.part[j] = *reinterpret_cast<const u4v*>(&ck.tm[j][m_row][8 * ph]);
       }
       low = mfma32_split<3>(tm.part, sr, low);
+    }
+    // [diag(E) T; B T] is finite, so the first row's product is not finite
+    // if any R of the column is not: v is not finite, or K S0 overflows
+    if constexpr (!KDA) {
+      const bool out = !(fabsf(low[0]) <= FLT_MAX);
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(out) != 0, 0)) return false;
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) {

@@ -304,3 +304,72 @@ def test_prefill_vanishing_decays_with_many_tiles(kda):
     state = gpool.buffer.cpu().numpy().view(np.float32)
     assert np.isfinite(o_gpu).all() and np.isfinite(state).all()
     assert rel_l2(o_gpu, o_ref) <= 1e-5 and rel_l2(state, ref.buf.view(np.float32)) <= 1e-5
+
+
+def _fp32_case(kda, B, HV, T, seed, states=None, HK=None):
+    """d = 128, FP32 state, identity slots: (oracle pool, GPU pool, inputs)."""
+    d, HK = 128, HK or HV
+    ref = orc.Pool(orc.KIND_FP32, d, d, 0, 1, B, HV)
+    S = np.zeros((B, HV, d, d), np.float32) if states is None else states
+    orc.pack(ref, 0, np.arange(B), S)
+    return ref, gpu_pool_from(ref, D), inputs.as_prefill(
+        inputs.decode_inputs(seed, T, B, HK, HV, d, kda=kda))
+
+
+def _bits(x):
+    return inputs.to_bf16_bits(np.float32(x))[0]
+
+
+def _scale_bf16(bits, factor):
+    """bf16 bit patterns times a power of two (exact)."""
+    return inputs.to_bf16_bits((bits.astype(np.uint32) << 16).view(np.float32) * np.float32(factor))
+
+
+@pytest.mark.parametrize("B", [2, 129])
+def test_prefill_gdn_growing_factors(B):
+    """Factors above one whose product over a chunk is beyond fp32, on a state
+    that is still zero: the state stays zero through them. In head 0 the
+    product from the chunk's start overflows, in head 1 only the one from its
+    second token on."""
+    HV, T = 2, 40
+    ref, gpool, inp = _fp32_case(False, B, HV, T, 801)
+    g, v = inp["g"].copy(), inp["v"].copy()
+    g[:, :12, 0] = _bits(10.0)
+    g[:, 0, 1] = _bits(-50.0)
+    g[:, 1:10, 1] = _bits(12.0)
+    v[:, :12] = 0
+    inp.update(g=g, v=v)
+    o_gpu, o_ref = _run(False, ref, gpool, np.arange(B), inp, None)
+    state = gpool.buffer.cpu().numpy().view(np.float32)
+    assert np.isfinite(o_gpu).all() and np.isfinite(state).all()
+    assert rel_l2(o_gpu, o_ref) <= 1e-6 and rel_l2(state, ref.buf.view(np.float32)) <= 1e-6
+
+
+@pytest.mark.parametrize("B", [2, 129])
+@pytest.mark.parametrize("kda", [False])
+def test_prefill_overflow_leaves_earlier_tokens(kda, B):
+    """Keys of norm 128: each token multiplies the state by up to |k|^2, which
+    leaves fp32 within the first chunk. The tokens before that are what they
+    are in the token-by-token form (whose rounding grows with the state: its
+    bar is looser here). A single large key in an otherwise ordinary chunk
+    overflows one token's read-outs and what follows it, nothing before."""
+    HV, T = 1, 16
+    S = inputs.synthetic_states(803, B, HV, 128)
+    ref, gpool, inp = _fp32_case(kda, B, HV, T, 803, S)
+    inp["k"] = _scale_bf16(inp["k"], 128.0)
+    o_gpu, o_ref = _run(kda, ref, gpool, np.arange(B), inp, None)
+    with np.errstate(all="ignore"):
+        top = np.abs(o_ref).max((0, 2, 3))
+    fine = np.flatnonzero(~(top < 1e30))
+    before = int(fine[0]) if fine.size else T
+    assert before < T  # it does overflow
+    for t in range(before):
+        assert rel_l2(o_gpu[:, t], o_ref[:, t]) <= 1e-4, t
+
+    ref, gpool, inp = _fp32_case(kda, B, HV, T, 805, S * np.float32(2.0 ** 70))
+    k = inp["k"].copy()
+    k[:, 9] = _scale_bf16(k[:, 9], 2.0 ** 70)
+    inp["k"] = k
+    o_gpu, o_ref = _run(kda, ref, gpool, np.arange(B), inp, None)
+    assert rel_l2(o_gpu[:, :9], o_ref[:, :9]) <= 1e-6
+    assert not np.isfinite(o_gpu[:, 10:]).any()
