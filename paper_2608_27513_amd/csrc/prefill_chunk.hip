@@ -31,9 +31,17 @@
 //   k~_t = k_t rho_t, q~_t = q_t rho_t, k^_s = k_s / rho_s
 // and, with S0' = diag(a_0 ... a_7) S0, the same formulas hold with L = G = 1:
 //   A_ts = beta_s k~_t.k^_s, S_C = diag(a_8 ... a_15) (S0' + K^^T U).
-// The eight-token products on either side of r must stay in [2^-96, 2^96];
-// a chunk where some channel leaves it (a zero decay included) runs token by
-// token too.
+// The products on either side of r must stay in [2^-96, 2^96]. A channel whose
+// decays leave it on one side (a zero decay included) is steep in this chunk:
+// k~.k^ then lacks its share between two tokens of that side, k_t k_s times the
+// product of the decays between them, which the waves that form A and B add by
+// themselves, and its rows for the products with the state take the chunk's
+// ends as references, where no inverse is needed: k_t G_t with S0, k_s L_{15,s}
+// with U, and S0 takes G_15 between the two. More than 8 such channels among
+// the 64 of a staging wave (or a product above the range) and the chunk runs
+// token by token. One steep channel at g = -9 in every head, FP32 state, before
+// (token by token) and now: B = 32, 250 tokens 835 -> 370 us (334 with none),
+// B = 8, 1024 tokens 1433 -> 431 (300), B = 256, 64 tokens 1530 -> 732 (646).
 //
 // Mapping. A workgroup of four waves owns one (request, value head) tile;
 // wave w holds columns 32 w .. 32 w + 31 of the state for all 128 channels, in
@@ -203,6 +211,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* base, in
                                            0x00020000);
 }
 
+// How a chunk is run, if not in the plain matrix form (a bit set).
+constexpr int kTokens = 1;  // token by token
+constexpr int kSteep = 2;   // KDA: channels in steep form beside the others
+constexpr int kSteepRows = 8;  // of the 64 channels and 8 tokens of a staging wave
+
 // LDS of one chunk's operands. GDN: kq holds the 16 rows of k, then of q, and
 // tm [U rows; O rows] as three bf16 parts. KDA: kq holds k~ and q~ in three
 // parts, kh k^ in three parts, tm the fp32 values (split when read).
@@ -222,7 +235,15 @@ struct alignas(16) ChunkLds<true> {
   float tm[32][kC];
   float pre[kD], fin[kD];
   float beta[kC];
-  int32_t flag[4], vflag[4];  // by staging wave; by wave, its columns of v
+  int32_t flag[4], vflag[4];  // kTokens, kSteep by staging wave; by wave, its columns of v
+  // steep channels: by staging wave, a bit per pair of channels (even, odd
+  // channels); their operands in its half of the tokens, in the order of the
+  // bits; and the factors that take the place of pre and fin
+  uint32_t steep[4][2];
+  struct {
+    float k[8], q[8], a[8];
+  } row[4][kSteepRows];
+  float pre_s[kD], mid_s[kD], fin_s[kD];
 };
 
 // SPLIT: eight waves a workgroup, four of which stage the next chunks into a
@@ -453,14 +474,15 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
   // the lane id, formed anew in each phase (see opaque)
   auto lane_now = [&]() __attribute__((always_inline)) { return opaque(t) & 63; };
 
-  auto flagged = [&](const typename P::Chunk& ck) __attribute__((always_inline)) -> bool {
+  // 0, or what a chunk's staging found (kTokens, kSteep)
+  auto form_of = [&](const typename P::Chunk& ck) __attribute__((always_inline)) -> int {
     int f;
     if constexpr (KDA)
       f = ck.flag[0] | ck.flag[1] | ck.flag[2] | ck.flag[3] | ck.vflag[0] | ck.vflag[1] |
           ck.vflag[2] | ck.vflag[3];
     else
       f = ck.flag;
-    return __builtin_amdgcn_readfirstlane(f) != 0;
+    return __builtin_amdgcn_readfirstlane(f);
   };
 
   // ---- GDN staging, wave-local: wave w stages chunk w
@@ -547,14 +569,12 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
 
   // ---- KDA staging by four waves in three steps, a barrier after each: waves
   // 0 and 1 take the first eight tokens, waves 2 and 3 the others
-  float ka[2][4];  // the lane's decays
   auto kda_operands = [&](typename P::Chunk& ck) __attribute__((always_inline)) {
     if constexpr (KDA) {
       const int half = wave >> 1;
       const int lane = lane_now(), ph = lane >> 5, l32 = lane & 31;
       // cum[i]: the channel's product between token 7 and token i of the lane's four
-      float cum[2][4];
-      float(&a)[2][4] = ka;
+      float cum[2][4], a[2][4];
       uint32_t bad = 0u;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -563,6 +583,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         bad |= nonfinite(in.kp[i]) | nonfinite(in.qp[i]);
       }
       float whole[2];
+      uint64_t low[2];  // the lanes of steep channels
 #pragma unroll
       for (int m = 0; m < 2; ++m) {
         const float mine = (a[m][0] * a[m][1]) * (a[m][2] * a[m][3]);
@@ -581,21 +602,35 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
             cum[m][i] = run;
           }
         }
+        bool below = false;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (!(cum[m][i] >= kRhoMin && cum[m][i] <= kRhoMax)) bad = 1u;
+        for (int i = 0; i < 4; ++i) {
+          if (!(cum[m][i] <= kRhoMax)) bad = 1u;
+          below = below || cum[m][i] < kRhoMin;
+        }
+        low[m] = __builtin_amdgcn_ballot_w64(below);
         whole[m] = run;
         if (!(run <= FLT_MAX)) bad = 1u;
       }
       const float beta = bf16_to_f32(static_cast<uint16_t>(in.beta));
       if (!(fabsf(beta) <= FLT_MAX)) bad = 1u;
-      const bool any = __builtin_amdgcn_ballot_w64(bad != 0u) != 0;
-      if (lane == 0) ck.flag[wave] = any ? 1 : 0;
+      int form = __builtin_amdgcn_ballot_w64(bad != 0u) != 0 ? kTokens : 0;
+      if (__builtin_expect((low[0] | low[1]) != 0, 0)) {
+        uint32_t steep[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          steep[m] = static_cast<uint32_t>(low[m]) | static_cast<uint32_t>(low[m] >> 32);
+          if (lane == 0) ck.steep[wave][m] = steep[m];
+        }
+        form |= kSteep;
+        if (__builtin_popcount(steep[0]) + __builtin_popcount(steep[1]) > kSteepRows) form |= kTokens;
+      }
+      if (lane == 0) ck.flag[wave] = form;
       uint32_t vbad = 0u;
 #pragma unroll
       for (int e = 0; e < 8; ++e) vbad |= nonfinite(in.v[KDA ? e : 0]);
       const bool v_flagged = __builtin_amdgcn_ballot_w64(vbad != 0u) != 0;
-      if (lane == 0) ck.vflag[wave] = v_flagged ? 1 : 0;
+      if (lane == 0) ck.vflag[wave] = v_flagged ? kTokens : 0;
       if (wave == 0 && lane < kC) ck.beta[lane] = beta;
       // the lanes of a channel's far tokens hold the product of all eight
       if ((half == 0) == (ph == 0))
@@ -624,26 +659,42 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
 #pragma unroll
         for (int j = 0; j < 3; ++j) *reinterpret_cast<uint32_t*>(ck.kh[j] + row) = s3[j];
       }
-    }
-  };
-  // one wave of each half of the rows: A = beta_s k~_t.k^_s, B = beta_s q~_t.k^_s;
-  // for a flagged chunk k, q and the decays themselves instead
-  auto kda_products = [&](typename P::Chunk& ck, int who) __attribute__((always_inline)) {
-    if constexpr (KDA) {
-      const int lane = lane_now();
-      if (__builtin_expect(flagged(ck), 0)) {
-        const int half = wave >> 1, ph = lane >> 5, l32 = lane & 31, first = 8 * half + 4 * ph;
-        const int at = row_at(first, 8 * (wave & 1) + (l32 >> 2)) + 4 * (l32 & 3);
+      if (__builtin_expect(form != kSteep, 1)) return;
+      // steep channels: the side of 1 / rho leaves the products (zero), and
+      // what they lack is left in row for kda_products
+      int at_row = 0;
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        const uint32_t steep = static_cast<uint32_t>(low[m]) | static_cast<uint32_t>(low[m] >> 32);
+        const int before = at_row + __builtin_popcount(steep & ((1u << l32) - 1u));
+        at_row += __builtin_popcount(steep);
+        if ((steep >> l32 & 1u) == 0u) continue;
+        auto& r = ck.row[wave][before];
+        const uint32_t keep = m ? 0x0000ffffu : 0xffff0000u;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          uint8_t* row = ck.kq[0] + (at ^ (i << 4)) + i * kRow;
-          *reinterpret_cast<uint32_t*>(row) = in.kp[i];
-          *reinterpret_cast<uint32_t*>(row + 16 * kRow) = in.qp[i];
-          reinterpret_cast<float2*>(ck.kq[NA > 1 ? 1 : 0])[(first + i) * (kD / 2) + 32 * (wave & 1) +
-                                                           l32] = make_float2(ka[0][i], ka[1][i]);
+          r.k[4 * ph + i] = m ? bf16_hi(in.kp[i]) : bf16_lo(in.kp[i]);
+          r.q[4 * ph + i] = m ? bf16_hi(in.qp[i]) : bf16_lo(in.qp[i]);
+          r.a[4 * ph + i] = a[m][i];
+          const int row = (at ^ (i << 4)) + i * kRow;
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            if (half == 0) {
+              *reinterpret_cast<uint32_t*>(ck.kq[KDA ? j : 0] + row) &= keep;
+              *reinterpret_cast<uint32_t*>(ck.kq[KDA ? j : 0] + row + 16 * kRow) &= keep;
+            } else {
+              *reinterpret_cast<uint32_t*>(ck.kh[j] + row) &= keep;
+            }
+          }
         }
-        return;
       }
+    }
+  };
+  // one wave of each half of the rows: A = beta_s k~_t.k^_s, B = beta_s q~_t.k^_s
+  auto kda_products = [&](typename P::Chunk& ck, int form, int who) __attribute__((always_inline)) {
+    if constexpr (KDA) {
+      if ((form & kTokens) != 0) return;
+      const int lane = lane_now();
       if (((wave ^ who) & 2) != 0) return;
       const int s = lane & 15, quad = lane >> 4, rows = (wave ^ who) & 1;
       f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -663,6 +714,34 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         acc = mfma16(fa[0], fb[1], acc);
         acc = mfma16(fa[0], fb[0], acc);
       }
+      if (__builtin_expect(form != 0, 0)) {
+        // steep channels, tokens of one half: k_t k_s (q_t k_s) times the
+        // product of the decays between the two
+#pragma unroll 1
+        for (int w = 0; w < 4; ++w) {
+          if (__builtin_amdgcn_readfirstlane(ck.flag[w]) == 0) continue;
+          const int n = __builtin_amdgcn_readfirstlane(__builtin_popcount(ck.steep[w][0]) +
+                                                       __builtin_popcount(ck.steep[w][1]));
+          const int half = w >> 1;
+          const bool mine = (s >> 3) == half && (quad >> 1) == half;
+#pragma unroll 1
+          for (int c = 0; c < n; ++c) {
+            const auto& r = ck.row[w][c];
+            float run = 1.0f, Lr[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int m = 0; m < 8; ++m) {
+              run = m <= (s & 7) ? 1.0f : run * r.a[m];
+              if ((quad & 1) == (m >> 2)) Lr[m & 3] = run;
+            }
+            const float ks = mine ? r.k[s & 7] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int tt = 4 * (quad & 1) + i;
+              acc[i] = fmaf(Lr[i] * ks, rows == 0 ? r.k[tt] : r.q[tt], acc[i]);
+            }
+          }
+        }
+      }
       const float bs = ck.beta[s];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -672,9 +751,87 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
       }
     }
   };
-  auto kda_solve = [&](typename P::Chunk& ck, int tb, int who) __attribute__((always_inline)) {
+  // a chunk that is not in the plain form, after its products: token by token,
+  // k, q and the decays themselves; else the steep channels' rows for the
+  // products with the state, referred to its two ends
+  auto kda_restage = [&](typename P::Chunk& ck, int form) __attribute__((always_inline)) {
     if constexpr (KDA) {
-      if (wave != who || flagged(ck)) return;
+      const int lane = lane_now(), half = wave >> 1, ph = lane >> 5, l32 = lane & 31;
+      const int first = 8 * half + 4 * ph, ch = 64 * (wave & 1) + 2 * l32;
+      const int at = row_at(first, 8 * (wave & 1) + (l32 >> 2)) + 4 * (l32 & 3);
+      float a[2][4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        a[0][i] = __expf(bf16_lo(in.gp[i]));
+        a[1][i] = __expf(bf16_hi(in.gp[i]));
+      }
+      if ((form & kTokens) != 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uint8_t* row = ck.kq[0] + (at ^ (i << 4)) + i * kRow;
+          *reinterpret_cast<uint32_t*>(row) = in.kp[i];
+          *reinterpret_cast<uint32_t*>(row + 16 * kRow) = in.qp[i];
+          reinterpret_cast<float2*>(ck.kq[NA > 1 ? 1 : 0])[(first + i) * (kD / 2) + (ch >> 1)] =
+              make_float2(a[0][i], a[1][i]);
+        }
+        return;
+      }
+      float G[2][4], E[2][4];  // products from the chunk's start to a token, from there to its end
+      uint32_t keep = 0u;      // the halves of a word whose channel is not steep
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        const float pre = ck.pre[ch + m], fin = ck.fin[ch + m];
+        const float mine = (a[m][0] * a[m][1]) * (a[m][2] * a[m][3]);
+        const float other = __shfl_xor(mine, 32, 64);
+        float run = (half ? pre : 1.0f) * (ph ? other : 1.0f);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          run *= a[m][i];
+          G[m][i] = run;
+        }
+        run = (half ? 1.0f : fin) * (ph ? 1.0f : other);
+#pragma unroll
+        for (int i = 3; i >= 0; --i) {
+          E[m][i] = run;
+          run *= a[m][i];
+        }
+        bool steep = false;
+#pragma unroll
+        for (int w = wave & 1; w < 4; w += 2)
+          if (ck.flag[w] != 0) steep = steep || (ck.steep[w][m] >> l32 & 1u) != 0u;
+        if (!steep) keep |= 0xffffu << (16 * m);
+        if (half == 0 && ph == 0) {
+          ck.pre_s[ch + m] = steep ? 1.0f : pre;
+          ck.mid_s[ch + m] = steep ? pre * fin : 1.0f;
+          ck.fin_s[ch + m] = steep ? 1.0f : fin;
+        }
+      }
+      if (keep == ~0u) return;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = (at ^ (i << 4)) + i * kRow;
+        const float k0 = bf16_lo(in.kp[i]), k1 = bf16_hi(in.kp[i]);
+        auto put = [&](uint8_t* base, const uint32_t (&s3)[3], int step) {
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            uint32_t* w = reinterpret_cast<uint32_t*>(base + j * step);
+            *w = (*w & keep) | (s3[j] & ~keep);
+          }
+        };
+        uint32_t s3[3];
+        split2(k0 * G[0][i], k1 * G[1][i], s3[0], s3[1], s3[2]);
+        put(ck.kq[0] + row, s3, sizeof(ck.kq[0]));
+        split2(bf16_lo(in.qp[i]) * G[0][i], bf16_hi(in.qp[i]) * G[1][i], s3[0], s3[1], s3[2]);
+        put(ck.kq[0] + row + 16 * kRow, s3, sizeof(ck.kq[0]));
+        split2(k0 * E[0][i], k1 * E[1][i], s3[0], s3[1], s3[2]);
+        put(ck.kh[0] + row, s3, sizeof(ck.kh[0]));
+      }
+    }
+  };
+  auto kda_solve = [&](typename P::Chunk& ck, int form, int tb,
+                       int who) __attribute__((always_inline)) {
+    if constexpr (KDA) {
+      if (wave != who || (form & kTokens) != 0) return;
       const int lane = lane_now(), s = lane & 15, quad = lane >> 4;
       float e4[4], um[4], om[4];
 #pragma unroll
@@ -711,9 +868,16 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         const int who = (tb0 / kC + h) & 3;
         if (tb0 < T) kda_operands(buf[0]);
         __syncthreads();
-        if (tb0 < T) kda_products(buf[0], who);
+        int form = 0;
+        if (tb0 < T) {
+          form = form_of(buf[0]);
+          kda_products(buf[0], form, who);
+        }
         __syncthreads();
-        if (tb0 < T) kda_solve(buf[0], tb0, who);
+        if (tb0 < T) {
+          if (__builtin_expect(form != 0, 0)) kda_restage(buf[0], form);
+          kda_solve(buf[0], form, tb0, who);
+        }
         __syncthreads();
       }
     };
@@ -834,7 +998,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
   // ---- one chunk of up to 16 tokens from token tb on this wave's columns
   // (vr: v of tokens 8 ph + e, this lane's column); false, and nothing done, if
   // some R of this wave's columns is not finite (GDN; KDA's flags have v)
-  auto run_chunk = [&](const typename P::Chunk& ck, int tb,
+  auto run_chunk = [&](const typename P::Chunk& ck, int tb, bool steep,
                        const uint32_t (&vr)[8]) __attribute__((always_inline)) -> bool {
     const int lane = lane_now(), ph = lane >> 5, l32 = lane & 31, col = 32 * wave + l32;
     // rows of the left-hand operands: lane l32 is row m of the 32; m % 16 bits
@@ -846,19 +1010,20 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
     // channels 32 bb + 16 (l32 / 16) + 8 p' + 4 r0 with l32 % 4 = 2 r0 + p'
     const int tr_s = 8 * ph + ((l32 >> 2) & 3);
     const int tr_ck = 2 * (l32 >> 4) + (l32 & 1), tr_half = ((l32 >> 1) & 1) * 8;
-    if constexpr (KDA) {
+    auto scale_rows = [&](const float* by) __attribute__((always_inline)) {
 #pragma unroll
       for (int bb = 0; bb < 4; ++bb)
 #pragma unroll
         for (int c2 = 0; c2 < 4; ++c2) {
           const float4 f = *reinterpret_cast<const float4*>(
-              &ck.pre[32 * bb + 16 * (c2 >> 1) + 8 * ph + 4 * (c2 & 1)]);
+              &by[32 * bb + 16 * (c2 >> 1) + 8 * ph + 4 * (c2 & 1)]);
           S[bb][4 * c2] *= f.x;
           S[bb][4 * c2 + 1] *= f.y;
           S[bb][4 * c2 + 2] *= f.z;
           S[bb][4 * c2 + 3] *= f.w;
         }
-    }
+    };
+    if constexpr (KDA) scale_rows(steep ? ck.pre_s : ck.pre);
     // [K; Q] S0: accumulators 0..7 are rows k_t, 8..15 rows q_t, t = 8 ph + e
     f16v acc, low;
 #pragma unroll
@@ -881,6 +1046,9 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
       mfma32_split<NA>(fa, sb, acc, low);
       // the operands of one step (GDN: two) at a time: registers
       if (KDA || (ks & 1)) __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (KDA) {
+      if (__builtin_expect(steep, 0)) scale_rows(ck.mid_s);
     }
     if constexpr (KDA) __syncthreads();  // tm is there (SPLIT: the other waves' first step is done)
     // R = V - G K S0; G Q S0 stays in acc[8 + e]
@@ -976,19 +1144,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
       }
       S[bb] = mfma32_split<NA>(fa, su, S[bb]);
     }
-    if constexpr (KDA) {
-#pragma unroll
-      for (int bb = 0; bb < 4; ++bb)
-#pragma unroll
-        for (int c2 = 0; c2 < 4; ++c2) {
-          const float4 f = *reinterpret_cast<const float4*>(
-              &ck.fin[32 * bb + 16 * (c2 >> 1) + 8 * ph + 4 * (c2 & 1)]);
-          S[bb][4 * c2] *= f.x;
-          S[bb][4 * c2 + 1] *= f.y;
-          S[bb][4 * c2 + 2] *= f.z;
-          S[bb][4 * c2 + 3] *= f.w;
-        }
-    }
+    if constexpr (KDA) scale_rows(steep ? ck.fin_s : ck.fin);
     return true;
   };
 
@@ -1012,7 +1168,8 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         load_v(tb, vr);
       }
       bool done = false;
-      if (!flagged(buf[c])) done = run_chunk(buf[c], tb, vr);
+      const int form = form_of(buf[c]);
+      if ((form & kTokens) == 0) done = run_chunk(buf[c], tb, form != 0, vr);
       if (__builtin_expect(!__builtin_amdgcn_readfirstlane(done ? 1 : 0), 0)) {
         run_tokens(buf[c], tb, n);
         if constexpr (KDA && SPLIT) {  // those of run_chunk
@@ -1031,9 +1188,12 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         const int who = (tb0 / kC + h) & 3;
         kda_operands(L[0]);
         __syncthreads();
-        kda_products(L[0], who);
+        const int form = form_of(L[0]);
+        kda_products(L[0], form, who);
         __syncthreads();
-        kda_solve(L[0], tb0, who);  // the other waves start on the chunk
+        if (__builtin_expect(form != 0, 0)) kda_restage(L[0], form);
+        kda_solve(L[0], form, tb0, who);  // the other waves start on the chunk
+        if (__builtin_expect(form != 0, 0)) __syncthreads();  // restaged
       } else {
         __syncthreads();
       }

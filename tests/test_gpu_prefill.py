@@ -373,3 +373,62 @@ def test_prefill_overflow_leaves_earlier_tokens(kda, B):
     o_gpu, o_ref = _run(kda, ref, gpool, np.arange(B), inp, None)
     assert rel_l2(o_gpu[:, :9], o_ref[:, :9]) <= 1e-6
     assert not np.isfinite(o_gpu[:, 10:]).any()
+
+
+# steep channels: one; a few of both halves of the channels, even and odd; as
+# many of one half as are kept beside the others, and one more; every channel
+STEEP = {"one": [37], "both_waves": [2, 5, 64, 127], "list_full": list(range(8, 16)),
+         "list_over": list(range(70, 79)), "all": list(range(128))}
+
+
+@pytest.mark.parametrize("B", [2, 257])
+@pytest.mark.parametrize("g0", [-9.5, -30.0, -100.0, -np.inf])
+@pytest.mark.parametrize("which", list(STEEP))
+def test_prefill_kda_steep_channels(which, g0, B):
+    """Channels whose decays over half a chunk leave the range of the matrix
+    form, beside ordinary ones: in every token, in the first or the second
+    half of a chunk only, at one token inside a half (in a chunk between
+    ordinary ones) and in a partial last chunk."""
+    HV, T, seed = 1, 74, 811
+    S = inputs.synthetic_states(seed, B, HV, 128)
+    ref, gpool, inp = _fp32_case(True, B, HV, T, seed, S)
+    g = inp["g"].copy()
+    for b, span in enumerate((slice(0, T), slice(16, 24), slice(24, 32), slice(20, 21),
+                              slice(64, T), slice(39, 41))):
+        for c in STEEP[which]:
+            g[b::6, span, 0, c] = _bits(g0)
+    inp["g"] = g
+    o_gpu, o_ref = _run(True, ref, gpool, np.arange(B), inp, None)
+    state = gpool.buffer.cpu().numpy().view(np.float32)
+    err, s_err = rel_l2(o_gpu, o_ref), rel_l2(state, ref.buf.view(np.float32))
+    _say(f"  {which} g={g0} B={B}: o rel-L2 {err:.2e} state rel-L2 {s_err:.2e}")
+    assert err <= 1e-6 and s_err <= 1e-6
+
+
+def test_prefill_kda_steep_channel_costs_little():
+    """One channel of 128 that decays steeply leaves the others in the matrix
+    form: 1.5 times the time of the batch without it here, 5 times if the
+    whole tile ran token by token."""
+    HV, B, T = 4, 2, 512
+    _, gpool, inp = _fp32_case(True, B, HV, T, 821)
+    ms = []
+    for steep in (False, True):
+        x = dict(inp, g=inp["g"].copy())
+        if steep:
+            x["g"][..., 7] = _bits(-9.0)
+        x, slots = dev_inputs(x), dev_i32(np.arange(B))
+        call = lambda: D.damp_state_prefill_kda(gpool, 0, slots, x["q"], x["k"], x["v"], x["g"],
+                                                x["beta"])
+        call()
+        runs = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(4):
+                call()
+            b.record()
+            b.synchronize()
+            runs.append(a.elapsed_time(b))
+        ms.append(min(runs))
+    _say(f"  {ms[0] / 4 * 1e3:.1f} us, with a steep channel {ms[1] / 4 * 1e3:.1f} us")
+    assert ms[1] <= 3 * ms[0]
