@@ -31,7 +31,7 @@
 //   k~_t = k_t rho_t, q~_t = q_t rho_t, k^_s = k_s / rho_s
 // and, with S0' = diag(a_0 ... a_7) S0, the same formulas hold with L = G = 1:
 //   A_ts = beta_s k~_t.k^_s, S_C = diag(a_8 ... a_15) (S0' + K^^T U).
-// The products on either side of r must stay in [2^-96, 2^96]. A channel whose
+// The products on either side of r must stay in [2^-80, 2^80]. A channel whose
 // decays leave it on one side (a zero decay included) is steep in this chunk:
 // k~.k^ then lacks its share between two tokens of that side, k_t k_s times the
 // product of the decays between them, which the waves that form A and B add by
@@ -39,9 +39,14 @@
 // ends as references, where no inverse is needed: k_t G_t with S0, k_s L_{15,s}
 // with U, and S0 takes G_15 between the two. More than 8 such channels among
 // the 64 of a staging wave (or a product above the range) and the chunk runs
-// token by token. One steep channel at g = -9 in every head, FP32 state, before
-// (token by token) and now: B = 32, 250 tokens 835 -> 370 us (334 with none),
-// B = 8, 1024 tokens 1433 -> 431 (300), B = 256, 64 tokens 1530 -> 732 (646).
+// token by token. So does one whose k, q, v or beta reaches 2^32, 2^32, 2^32,
+// 2^16, or that has a column whose v is below 2^-24 but not zero: so k^ and k^ U
+// stay finite, and the third parts of S0' and R stay above the smallest normal
+// number, below which the products drop them. Nor may |A| pass 2^7 (it is looked
+// at where k, beta or a decay is above one): so T, whose entries reach
+// (1 + |A|)^14, stays finite. One steep channel at g = -9 in every head, FP32 state, before
+// (token by token) and now: B = 32, 250 tokens 835 -> 390 us (334 with none),
+// B = 8, 1024 tokens 1433 -> 470 (302), B = 256, 64 tokens 1530 -> 721 (655).
 //
 // Mapping. A workgroup of four waves owns one (request, value head) tile;
 // wave w holds columns 32 w .. 32 w + 31 of the state for all 128 channels, in
@@ -93,7 +98,8 @@ constexpr int kC = 16;    // tokens of a chunk
 constexpr int kD = 128;
 constexpr int kRow = 256;  // bytes of a row of 128 bf16
 constexpr int kPitch = 68;  // floats of a row of half the tile's columns in transit
-constexpr float kRhoMin = 0x1p-96f, kRhoMax = 0x1p96f;
+constexpr float kRhoMin = 0x1p-80f, kRhoMax = 0x1p80f;
+constexpr float kBetaMax = 0x1p16f, kKeysMax = 0x1p7f;  // KDA's matrix form (see above)
 
 __device__ __forceinline__ f16v mfma32(u4v a, u4v b, f16v c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8v, a),
@@ -202,6 +208,16 @@ __device__ __forceinline__ int row_at(int r, int ck) { return r * kRow + ((ck ^ 
 __device__ __forceinline__ uint32_t nonfinite(uint32_t w) {
   return ((w & 0x7f807f80u) + 0x00800080u) & 0x80008000u;
 }
+// The bits of the largest magnitude among bf16 pairs.
+struct MaxBits {
+  typedef uint16_t us2 __attribute__((ext_vector_type(2)));
+  us2 pair = {0, 0};
+  __device__ __forceinline__ void add(uint32_t w) {
+    pair = __builtin_elementwise_max(pair, __builtin_bit_cast(us2, w & 0x7fff7fffu));
+  }
+  __device__ __forceinline__ uint32_t bits() const { return pair.x > pair.y ? pair.x : pair.y; }
+};
+constexpr uint32_t bf16_pow2(int e) { return static_cast<uint32_t>(127 + e) << 7; }
 
 // `n` rows of `bytes` bytes, `step` bytes apart, as a raw buffer that ends with
 // the last row: reads past it return zero and writes are dropped.
@@ -214,6 +230,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* base, in
 // How a chunk is run, if not in the plain matrix form (a bit set).
 constexpr int kTokens = 1;  // token by token
 constexpr int kSteep = 2;   // KDA: channels in steep form beside the others
+constexpr int kKeys = 4;    // KDA: |A| may be large and is looked at
 constexpr int kSteepRows = 8;  // of the 64 channels and 8 tokens of a staging wave
 
 // LDS of one chunk's operands. GDN: kq holds the 16 rows of k, then of q, and
@@ -233,9 +250,9 @@ struct alignas(16) ChunkLds<true> {
   uint8_t kq[3][32 * kRow];
   uint8_t kh[3][16 * kRow];
   float tm[32][kC];
-  float pre[kD], fin[kD];
+  alignas(16) float pre[kD], fin[kD];
   float beta[kC];
-  int32_t flag[4], vflag[4];  // kTokens, kSteep by staging wave; by wave, its columns of v
+  int32_t flag[4], vflag[4];  // form by staging wave; kTokens by wave, its columns of v
   // steep channels: by staging wave, a bit per pair of channels (even, odd
   // channels); their operands in its half of the tokens, in the order of the
   // bits; and the factors that take the place of pre and fin
@@ -243,7 +260,8 @@ struct alignas(16) ChunkLds<true> {
   struct {
     float k[8], q[8], a[8];
   } row[4][kSteepRows];
-  float pre_s[kD], mid_s[kD], fin_s[kD];
+  alignas(16) float pre_s[kD], mid_s[kD], fin_s[kD];
+  int32_t grows;  // with kKeys: 0, or kTokens if A is out of range
 };
 
 // SPLIT: eight waves a workgroup, four of which stage the next chunks into a
@@ -474,7 +492,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
   // the lane id, formed anew in each phase (see opaque)
   auto lane_now = [&]() __attribute__((always_inline)) { return opaque(t) & 63; };
 
-  // 0, or what a chunk's staging found (kTokens, kSteep)
+  // 0, or what a chunk's staging found
   auto form_of = [&](const typename P::Chunk& ck) __attribute__((always_inline)) -> int {
     int f;
     if constexpr (KDA)
@@ -483,6 +501,13 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
     else
       f = ck.flag;
     return __builtin_amdgcn_readfirstlane(f);
+  };
+  // KDA: the same once the products are there
+  auto with_grows = [&](const typename P::Chunk& ck, int form) __attribute__((always_inline)) -> int {
+    if constexpr (KDA) {
+      if (__builtin_expect((form & kKeys) != 0, 0)) form |= __builtin_amdgcn_readfirstlane(ck.grows);
+    }
+    return form;
   };
 
   // ---- GDN staging, wave-local: wave w stages chunk w
@@ -575,12 +600,15 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
       const int lane = lane_now(), ph = lane >> 5, l32 = lane & 31;
       // cum[i]: the channel's product between token 7 and token i of the lane's four
       float cum[2][4], a[2][4];
-      uint32_t bad = 0u;
+      MaxBits kmax, qmax;
+      float amax = 0.0f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         a[0][i] = __expf(bf16_lo(in.gp[i]));
         a[1][i] = __expf(bf16_hi(in.gp[i]));
-        bad |= nonfinite(in.kp[i]) | nonfinite(in.qp[i]);
+        amax = fmaxf(fmaxf(a[0][i], a[1][i]), amax);
+        kmax.add(in.kp[i]);
+        qmax.add(in.qp[i]);
       }
       float whole[2];
       uint64_t low[2];  // the lanes of steep channels
@@ -602,19 +630,26 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
             cum[m][i] = run;
           }
         }
-        bool below = false;
+        float least = kRhoMax;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (!(cum[m][i] <= kRhoMax)) bad = 1u;
-          below = below || cum[m][i] < kRhoMin;
-        }
-        low[m] = __builtin_amdgcn_ballot_w64(below);
-        whole[m] = run;
-        if (!(run <= FLT_MAX)) bad = 1u;
+        for (int i = 0; i < 4; ++i) least = fminf(least, cum[m][i]);
+        low[m] = __builtin_amdgcn_ballot_w64(least < kRhoMin);
+        whole[m] = run;  // a NaN in cum is in it too
       }
       const float beta = bf16_to_f32(static_cast<uint16_t>(in.beta));
-      if (!(fabsf(beta) <= FLT_MAX)) bad = 1u;
-      int form = __builtin_amdgcn_ballot_w64(bad != 0u) != 0 ? kTokens : 0;
+      const uint32_t kbits = kmax.bits();
+      bool bad = qmax.bits() >= bf16_pow2(32) || !(whole[0] <= FLT_MAX) || !(whole[1] <= FLT_MAX);
+      int form = 0;
+      // |k|, |beta| and the decays at most 1: |A| <= 128 = kKeysMax
+      const bool wide = kbits > bf16_pow2(0) || !(fabsf(beta) <= 1.0f) || amax > 1.0f;
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(wide) != 0, 0)) {
+        form = kKeys;
+        float top = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) top = fmaxf(fmaxf(cum[0][i], cum[1][i]), top);
+        bad = bad || kbits >= bf16_pow2(32) || !(fabsf(beta) <= kBetaMax) || top > kRhoMax;
+      }
+      if (__builtin_amdgcn_ballot_w64(bad) != 0) form |= kTokens;
       if (__builtin_expect((low[0] | low[1]) != 0, 0)) {
         uint32_t steep[2];
 #pragma unroll
@@ -626,10 +661,14 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         if (__builtin_popcount(steep[0]) + __builtin_popcount(steep[1]) > kSteepRows) form |= kTokens;
       }
       if (lane == 0) ck.flag[wave] = form;
-      uint32_t vbad = 0u;
+      uint32_t vmax = 0u;  // bits of the largest |v| of the lane's tokens
 #pragma unroll
-      for (int e = 0; e < 8; ++e) vbad |= nonfinite(in.v[KDA ? e : 0]);
-      const bool v_flagged = __builtin_amdgcn_ballot_w64(vbad != 0u) != 0;
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t av = in.v[KDA ? e : 0] & 0x7fffu;
+        vmax = av > vmax ? av : vmax;
+      }
+      const bool v_out = vmax != 0u && vmax - bf16_pow2(-24) >= bf16_pow2(32) - bf16_pow2(-24);
+      const bool v_flagged = __builtin_amdgcn_ballot_w64(v_out) != 0;
       if (lane == 0) ck.vflag[wave] = v_flagged ? kTokens : 0;
       if (wave == 0 && lane < kC) ck.beta[lane] = beta;
       // the lanes of a channel's far tokens hold the product of all eight
@@ -659,7 +698,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
 #pragma unroll
         for (int j = 0; j < 3; ++j) *reinterpret_cast<uint32_t*>(ck.kh[j] + row) = s3[j];
       }
-      if (__builtin_expect(form != kSteep, 1)) return;
+      if (__builtin_expect((form & (kSteep | kTokens)) != kSteep, 1)) return;
       // steep channels: the side of 1 / rho leaves the products (zero), and
       // what they lack is left in row for kda_products
       int at_row = 0;
@@ -714,12 +753,12 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         acc = mfma16(fa[0], fb[1], acc);
         acc = mfma16(fa[0], fb[0], acc);
       }
-      if (__builtin_expect(form != 0, 0)) {
+      if (__builtin_expect((form & kSteep) != 0, 0)) {
         // steep channels, tokens of one half: k_t k_s (q_t k_s) times the
         // product of the decays between the two
 #pragma unroll 1
         for (int w = 0; w < 4; ++w) {
-          if (__builtin_amdgcn_readfirstlane(ck.flag[w]) == 0) continue;
+          if ((__builtin_amdgcn_readfirstlane(ck.flag[w]) & kSteep) == 0) continue;
           const int n = __builtin_amdgcn_readfirstlane(__builtin_popcount(ck.steep[w][0]) +
                                                        __builtin_popcount(ck.steep[w][1]));
           const int half = w >> 1;
@@ -747,15 +786,23 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
       for (int i = 0; i < 4; ++i) {
         const int tt = 4 * quad + i;
         const bool in_tri = rows == 0 ? s < tt : s <= tt;
-        ck.tm[16 * rows + tt][s] = in_tri ? bs * acc[i] : 0.0f;
+        acc[i] = in_tri ? bs * acc[i] : 0.0f;
+        ck.tm[16 * rows + tt][s] = acc[i];
+      }
+      if (__builtin_expect((form & kKeys) != 0, 0) && rows == 0) {
+        const float sum = (fabsf(acc[0]) + fabsf(acc[1])) + (fabsf(acc[2]) + fabsf(acc[3]));
+        const bool grows = __builtin_amdgcn_ballot_w64(!(sum <= kKeysMax)) != 0;
+        if (lane == 0) ck.grows = grows ? kTokens : 0;
       }
     }
   };
-  // a chunk that is not in the plain form, after its products: token by token,
-  // k, q and the decays themselves; else the steep channels' rows for the
-  // products with the state, referred to its two ends
+  // a chunk that is not in the plain form, after its products. Token by token:
+  // k and q themselves in the first part, the decays of even and odd channels in
+  // the second. Else the steep channels' rows for the products with the state,
+  // referred to the chunk's two ends
   auto kda_restage = [&](typename P::Chunk& ck, int form) __attribute__((always_inline)) {
     if constexpr (KDA) {
+      if ((form & (kTokens | kSteep)) == 0) return;
       const int lane = lane_now(), half = wave >> 1, ph = lane >> 5, l32 = lane & 31;
       const int first = 8 * half + 4 * ph, ch = 64 * (wave & 1) + 2 * l32;
       const int at = row_at(first, 8 * (wave & 1) + (l32 >> 2)) + 4 * (l32 & 3);
@@ -771,8 +818,9 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
           uint8_t* row = ck.kq[0] + (at ^ (i << 4)) + i * kRow;
           *reinterpret_cast<uint32_t*>(row) = in.kp[i];
           *reinterpret_cast<uint32_t*>(row + 16 * kRow) = in.qp[i];
-          reinterpret_cast<float2*>(ck.kq[NA > 1 ? 1 : 0])[(first + i) * (kD / 2) + (ch >> 1)] =
-              make_float2(a[0][i], a[1][i]);
+          row += sizeof(ck.kq[0]);
+          *reinterpret_cast<uint32_t*>(row) = __float_as_uint(a[0][i]);
+          *reinterpret_cast<uint32_t*>(row + 16 * kRow) = __float_as_uint(a[1][i]);
         }
         return;
       }
@@ -798,7 +846,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         bool steep = false;
 #pragma unroll
         for (int w = wave & 1; w < 4; w += 2)
-          if (ck.flag[w] != 0) steep = steep || (ck.steep[w][m] >> l32 & 1u) != 0u;
+          if ((ck.flag[w] & kSteep) != 0) steep = steep || (ck.steep[w][m] >> l32 & 1u) != 0u;
         if (!steep) keep |= 0xffffu << (16 * m);
         if (half == 0 && ph == 0) {
           ck.pre_s[ch + m] = steep ? 1.0f : pre;
@@ -875,8 +923,9 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         }
         __syncthreads();
         if (tb0 < T) {
-          if (__builtin_expect(form != 0, 0)) kda_restage(buf[0], form);
+          form = with_grows(buf[0], form);
           kda_solve(buf[0], form, tb0, who);
+          if (__builtin_expect(form != 0, 0)) kda_restage(buf[0], form);
         }
         __syncthreads();
       }
@@ -937,7 +986,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
   }
 
   // ---- one flagged chunk token by token in fp32 (n tokens from token tb):
-  // rows of k and q in bf16 from LDS; KDA's decays in fp32 from LDS
+  // rows of k and q in bf16 and KDA's decays in fp32 from LDS
   auto run_tokens = [&](const typename P::Chunk& ck, int tb, int n) __attribute__((always_inline)) {
     const uint8_t* kq = ck.kq[0];
     const int lane = lane_now(), ph = lane >> 5, col = 32 * wave + (lane & 31);
@@ -949,15 +998,15 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
       for (int bb = 0; bb < 4; ++bb)
 #pragma unroll
         for (int cc = 0; cc < 2; ++cc) {
-          const int piece = 4 * bb + 2 * cc + ph;
           const uint8_t* row = kq + (at ^ ((4 * bb + 2 * cc) << 4));
           const u4v k8 = *reinterpret_cast<const u4v*>(row);
           const u4v q8 = *reinterpret_cast<const u4v*>(row + 16 * kRow);
           float a8[8];
           if constexpr (KDA) {
-            const float* ar = reinterpret_cast<const float*>(ck.kq[NA > 1 ? 1 : 0]) + tok * kD + 8 * piece;
+            const u4v a0 = *reinterpret_cast<const u4v*>(row + sizeof(ck.kq[0]));
+            const u4v a1 = *reinterpret_cast<const u4v*>(row + sizeof(ck.kq[0]) + 16 * kRow);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) a8[e] = ar[e];
+            for (int e = 0; e < 8; ++e) a8[e] = __uint_as_float(e & 1 ? a1[e >> 1] : a0[e >> 1]);
           } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e) a8[e] = ck.a[tok];
@@ -1168,8 +1217,8 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         load_v(tb, vr);
       }
       bool done = false;
-      const int form = form_of(buf[c]);
-      if ((form & kTokens) == 0) done = run_chunk(buf[c], tb, form != 0, vr);
+      const int form = with_grows(buf[c], form_of(buf[c]));
+      if ((form & kTokens) == 0) done = run_chunk(buf[c], tb, (form & kSteep) != 0, vr);
       if (__builtin_expect(!__builtin_amdgcn_readfirstlane(done ? 1 : 0), 0)) {
         run_tokens(buf[c], tb, n);
         if constexpr (KDA && SPLIT) {  // those of run_chunk
@@ -1188,12 +1237,15 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         const int who = (tb0 / kC + h) & 3;
         kda_operands(L[0]);
         __syncthreads();
-        const int form = form_of(L[0]);
+        int form = form_of(L[0]);
         kda_products(L[0], form, who);
         __syncthreads();
-        if (__builtin_expect(form != 0, 0)) kda_restage(L[0], form);
+        form = with_grows(L[0], form);
         kda_solve(L[0], form, tb0, who);  // the other waves start on the chunk
-        if (__builtin_expect(form != 0, 0)) __syncthreads();  // restaged
+        if (__builtin_expect(form != 0, 0)) {
+          kda_restage(L[0], form);
+          __syncthreads();
+        }
       } else {
         __syncthreads();
       }

@@ -346,7 +346,7 @@ def test_prefill_gdn_growing_factors(B):
 
 
 @pytest.mark.parametrize("B", [2, 129])
-@pytest.mark.parametrize("kda", [False])
+@pytest.mark.parametrize("kda", [False, True])
 def test_prefill_overflow_leaves_earlier_tokens(kda, B):
     """Keys of norm 128: each token multiplies the state by up to |k|^2, which
     leaves fp32 within the first chunk. The tokens before that are what they
@@ -432,3 +432,27 @@ def test_prefill_kda_steep_channel_costs_little():
         ms.append(min(runs))
     _say(f"  {ms[0] / 4 * 1e3:.1f} us, with a steep channel {ms[1] / 4 * 1e3:.1f} us")
     assert ms[1] <= 3 * ms[0]
+
+
+@pytest.mark.parametrize("B", [2, 129])
+@pytest.mark.parametrize("power", [100, 60, 33, 28, -20, -25, -60, -90])
+@pytest.mark.parametrize("kda", [False, True])
+def test_prefill_scale_of_state_and_values(kda, power, B):
+    """The recurrence is linear in (state, v): their scale costs no precision,
+    from where a chunk's products would overflow to where a part of a split
+    would fall below the normal numbers. Some of KDA's channels decay by 2^-79
+    on either side of a chunk's middle, just inside the range of the matrix
+    form."""
+    HV, T, seed = 2, 40, 831
+    S = inputs.synthetic_states(seed, B, HV, 128) * np.float32(2.0 ** power)
+    ref, gpool, inp = _fp32_case(kda, B, HV, T, seed, S)
+    inp["v"] = _scale_bf16(inp["v"], 2.0 ** power)
+    if kda:
+        g = inp["g"].copy()
+        g[..., 3::16] = _bits(-79 * np.log(2.0) / 8)
+        inp["g"] = g
+    o_gpu, o_ref = _run(kda, ref, gpool, np.arange(B), inp, None)
+    state = gpool.buffer.cpu().numpy().view(np.float32)
+    err, s_err = rel_l2(o_gpu, o_ref), rel_l2(state, ref.buf.view(np.float32))
+    _say(f"  kda={kda} 2^{power} B={B}: o rel-L2 {err:.2e} state rel-L2 {s_err:.2e}")
+    assert err <= 1e-6 and s_err <= 1e-6
