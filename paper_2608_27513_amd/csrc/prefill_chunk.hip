@@ -34,19 +34,19 @@
 // The products on either side of r must stay in [2^-80, 2^80]. A channel whose
 // decays leave it on one side (a zero decay included) is steep in this chunk:
 // k~.k^ then lacks its share between two tokens of that side, k_t k_s times the
-// product of the decays between them, which the waves that form A and B add by
-// themselves, and its rows for the products with the state take the chunk's
-// ends as references, where no inverse is needed: k_t G_t with S0, k_s L_{15,s}
-// with U, and S0 takes G_15 between the two. More than 8 such channels among
-// the 64 of a staging wave (or a product above the range) and the chunk runs
-// token by token. So does one whose k, q, v or beta reaches 2^32, 2^32, 2^32,
-// 2^16, or that has a column whose v is below 2^-24 but not zero: so k^ and k^ U
-// stay finite, and the third parts of S0' and R stay above the smallest normal
-// number, below which the products drop them. Nor may |A| pass 2^7 (it is looked
-// at where k, beta or a decay is above one): so T, whose entries reach
-// (1 + |A|)^14, stays finite. One steep channel at g = -9 in every head, FP32 state, before
-// (token by token) and now: B = 32, 250 tokens 835 -> 390 us (334 with none),
-// B = 8, 1024 tokens 1433 -> 470 (302), B = 256, 64 tokens 1530 -> 721 (655).
+// product of the decays between them, which the wave that stages them sums by
+// itself, and its rows for the products with the state take the chunk's ends as
+// references, where no inverse is needed: k_t G_t with S0, k_s L_{15,s} with U,
+// and S0 takes G_15 between the two. A chunk runs token by token if a product
+// passes 2^80, if its k, q, v or beta reaches 2^32, 2^32, 2^32, 2^16 or a column
+// of its v is below 2^-24 but not zero: so k^ and k^ U stay finite, and the
+// third parts of S0' and R stay above the smallest normal number, below which
+// the products drop them. Nor may |A| pass 2^7 (it is looked at where k, beta or
+// a decay is above one): so T, whose entries reach (1 + |A|)^14, stays finite.
+// One channel at g = -9 in every head, FP32 state, token by token and in this
+// form: B = 32, 250 tokens 835 -> 372 us (334 with none), B = 8, 1024 tokens
+// 1433 -> 465 (307), B = 256, 64 tokens 1530 -> 728 (667). Every channel: 785 ->
+// 575, 1433 -> 839, 1536 -> 1077.
 //
 // Mapping. A workgroup of four waves owns one (request, value head) tile;
 // wave w holds columns 32 w .. 32 w + 31 of the state for all 128 channels, in
@@ -195,6 +195,14 @@ __device__ __forceinline__ f16v mfma32_split(const u4v* a, const Split8& b, f16v
   return mfma32(a[0], b.part[0], s);
 }
 
+// The value N lanes before in the row of 16 lanes, 1 where there is none or the
+// lane's bank of four is not in BANKS.
+template <int N, int BANKS>
+__device__ __forceinline__ float lanes_before(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(1.0f), __float_as_int(x),
+                                                    0x110 + N, 0xf, BANKS, false));
+}
+
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
   __builtin_amdgcn_wave_barrier();
@@ -231,7 +239,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* base, in
 constexpr int kTokens = 1;  // token by token
 constexpr int kSteep = 2;   // KDA: channels in steep form beside the others
 constexpr int kKeys = 4;    // KDA: |A| may be large and is looked at
-constexpr int kSteepRows = 8;  // of the 64 channels and 8 tokens of a staging wave
+constexpr int kSteepBatch = 8;  // steep channels that a staging wave takes at a time
 
 // LDS of one chunk's operands. GDN: kq holds the 16 rows of k, then of q, and
 // tm [U rows; O rows] as three bf16 parts. KDA: kq holds k~ and q~ in three
@@ -253,13 +261,13 @@ struct alignas(16) ChunkLds<true> {
   alignas(16) float pre[kD], fin[kD];
   float beta[kC];
   int32_t flag[4], vflag[4];  // form by staging wave; kTokens by wave, its columns of v
-  // steep channels: by staging wave, a bit per pair of channels (even, odd
-  // channels); their operands in its half of the tokens, in the order of the
-  // bits; and the factors that take the place of pre and fin
+  // steep channels, by staging wave: a bit per pair of channels (even, odd
+  // channels); some of them at its tokens (k, q, a); their sums for A and B
+  // between its tokens s and t, at 8 s + t; and for all, the factors that take
+  // the place of pre and fin
   uint32_t steep[4][2];
-  struct {
-    float k[8], q[8], a[8];
-  } row[4][kSteepRows];
+  float4 row[4][kSteepBatch][8];
+  float2 sum[4][64];
   alignas(16) float pre_s[kD], mid_s[kD], fin_s[kD];
   int32_t grows;  // with kKeys: 0, or kTokens if A is out of range
 };
@@ -658,7 +666,6 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
           if (lane == 0) ck.steep[wave][m] = steep[m];
         }
         form |= kSteep;
-        if (__builtin_popcount(steep[0]) + __builtin_popcount(steep[1]) > kSteepRows) form |= kTokens;
       }
       if (lane == 0) ck.flag[wave] = form;
       uint32_t vmax = 0u;  // bits of the largest |v| of the lane's tokens
@@ -699,22 +706,20 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         for (int j = 0; j < 3; ++j) *reinterpret_cast<uint32_t*>(ck.kh[j] + row) = s3[j];
       }
       if (__builtin_expect((form & (kSteep | kTokens)) != kSteep, 1)) return;
-      // steep channels: the side of 1 / rho leaves the products (zero), and
-      // what they lack is left in row for kda_products
-      int at_row = 0;
+      // steep channels: the side of 1 / rho leaves the products (zero); what
+      // they lack there is summed here, token s = lane / 8 with t = lane % 8
+      uint32_t steep[2];
+      int rank[2], total = 0;  // of the lane's channels, -1: not steep
 #pragma unroll
       for (int m = 0; m < 2; ++m) {
-        const uint32_t steep = static_cast<uint32_t>(low[m]) | static_cast<uint32_t>(low[m] >> 32);
-        const int before = at_row + __builtin_popcount(steep & ((1u << l32) - 1u));
-        at_row += __builtin_popcount(steep);
-        if ((steep >> l32 & 1u) == 0u) continue;
-        auto& r = ck.row[wave][before];
+        steep[m] = static_cast<uint32_t>(low[m]) | static_cast<uint32_t>(low[m] >> 32);
+        const bool own = (steep[m] >> l32 & 1u) != 0u;
+        rank[m] = own ? total + __builtin_popcount(steep[m] & ((1u << l32) - 1u)) : -1;
+        total += __builtin_popcount(steep[m]);
+        if (!own) continue;
         const uint32_t keep = m ? 0x0000ffffu : 0xffff0000u;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          r.k[4 * ph + i] = m ? bf16_hi(in.kp[i]) : bf16_lo(in.kp[i]);
-          r.q[4 * ph + i] = m ? bf16_hi(in.qp[i]) : bf16_lo(in.qp[i]);
-          r.a[4 * ph + i] = a[m][i];
           const int row = (at ^ (i << 4)) + i * kRow;
 #pragma unroll
           for (int j = 0; j < 3; ++j) {
@@ -727,6 +732,40 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
           }
         }
       }
+      const int ts = lane >> 3, tt = lane & 7;
+      float2 sum = make_float2(0.0f, 0.0f);
+#pragma unroll 1
+      for (int first_c = 0; first_c < total; first_c += kSteepBatch) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const int c = rank[m] - first_c;
+          if (rank[m] < first_c || c >= kSteepBatch) continue;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            ck.row[wave][c][4 * ph + i] = make_float4(m ? bf16_hi(in.kp[i]) : bf16_lo(in.kp[i]),
+                                                      m ? bf16_hi(in.qp[i]) : bf16_lo(in.qp[i]),
+                                                      a[m][i], 0.0f);
+        }
+        wave_sync();
+        const int n = total - first_c < kSteepBatch ? total - first_c : kSteepBatch;
+#pragma unroll 2
+        for (int c = 0; c < n; ++c) {
+          const float4 kqa = ck.row[wave][c][tt];
+          const float ks = ck.row[wave][c][ts].x;
+          // the product of the decays of the tokens s + 1 .. t, over eight lanes
+          float run = tt > ts ? kqa.z : 1.0f;
+          const float by1 = lanes_before<1, 0xf>(run);
+          run *= tt >= 1 ? by1 : 1.0f;
+          const float by2 = lanes_before<2, 0xf>(run);
+          run *= tt >= 2 ? by2 : 1.0f;
+          run *= lanes_before<4, 0xa>(run);
+          const float f = run * ks;
+          sum.x = fmaf(f, kqa.x, sum.x);
+          sum.y = fmaf(f, kqa.y, sum.y);
+        }
+        wave_sync();
+      }
+      ck.sum[wave][lane] = sum;
     }
   };
   // one wave of each half of the rows: A = beta_s k~_t.k^_s, B = beta_s q~_t.k^_s
@@ -754,30 +793,14 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         acc = mfma16(fa[0], fb[0], acc);
       }
       if (__builtin_expect((form & kSteep) != 0, 0)) {
-        // steep channels, tokens of one half: k_t k_s (q_t k_s) times the
-        // product of the decays between the two
-#pragma unroll 1
-        for (int w = 0; w < 4; ++w) {
-          if ((__builtin_amdgcn_readfirstlane(ck.flag[w]) & kSteep) == 0) continue;
-          const int n = __builtin_amdgcn_readfirstlane(__builtin_popcount(ck.steep[w][0]) +
-                                                       __builtin_popcount(ck.steep[w][1]));
-          const int half = w >> 1;
-          const bool mine = (s >> 3) == half && (quad >> 1) == half;
-#pragma unroll 1
-          for (int c = 0; c < n; ++c) {
-            const auto& r = ck.row[w][c];
-            float run = 1.0f, Lr[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        const int half = quad >> 1;
 #pragma unroll
-            for (int m = 0; m < 8; ++m) {
-              run = m <= (s & 7) ? 1.0f : run * r.a[m];
-              if ((quad & 1) == (m >> 2)) Lr[m & 3] = run;
-            }
-            const float ks = mine ? r.k[s & 7] : 0.0f;
+        for (int w = 2 * half; w < 2 * half + 2; ++w) {
+          if ((s >> 3) != half || (ck.flag[w] & kSteep) == 0) continue;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int tt = 4 * (quad & 1) + i;
-              acc[i] = fmaf(Lr[i] * ks, rows == 0 ? r.k[tt] : r.q[tt], acc[i]);
-            }
+          for (int i = 0; i < 4; ++i) {
+            const float2 x = ck.sum[w][8 * (s & 7) + 4 * (quad & 1) + i];
+            acc[i] += rows == 0 ? x.x : x.y;
           }
         }
       }
@@ -1072,7 +1095,11 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
           S[bb][4 * c2 + 3] *= f.w;
         }
     };
+    // with three workgroups a CU the factors' reads are kept together: mixed
+    // with the splits they took one register group in turn (297 -> 292 us at
+    // B = 32, 250 tokens); alone on its SIMD a wave is better with the mix
     if constexpr (KDA) scale_rows(steep ? ck.pre_s : ck.pre);
+    if constexpr (KDA && !SPLIT) __builtin_amdgcn_sched_barrier(0);
     // [K; Q] S0: accumulators 0..7 are rows k_t, 8..15 rows q_t, t = 8 ph + e
     f16v acc, low;
 #pragma unroll
@@ -1193,6 +1220,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
       }
       S[bb] = mfma32_split<NA>(fa, su, S[bb]);
     }
+    if constexpr (KDA && !SPLIT) __builtin_amdgcn_sched_barrier(0);
     if constexpr (KDA) scale_rows(steep ? ck.fin_s : ck.fin);
     return true;
   };
@@ -1240,12 +1268,12 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         int form = form_of(L[0]);
         kda_products(L[0], form, who);
         __syncthreads();
-        form = with_grows(L[0], form);
-        kda_solve(L[0], form, tb0, who);  // the other waves start on the chunk
         if (__builtin_expect(form != 0, 0)) {
+          form = with_grows(L[0], form);
           kda_restage(L[0], form);
           __syncthreads();
         }
+        kda_solve(L[0], form, tb0, who);  // the other waves start on the chunk
       } else {
         __syncthreads();
       }

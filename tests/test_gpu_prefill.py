@@ -376,9 +376,9 @@ def test_prefill_overflow_leaves_earlier_tokens(kda, B):
 
 
 # steep channels: one; a few of both halves of the channels, even and odd; as
-# many of one half as are kept beside the others, and one more; every channel
-STEEP = {"one": [37], "both_waves": [2, 5, 64, 127], "list_full": list(range(8, 16)),
-         "list_over": list(range(70, 79)), "all": list(range(128))}
+# many of one half as are taken at a time, and one more; every channel
+STEEP = {"one": [37], "both_waves": [2, 5, 64, 127], "batch": list(range(8, 16)),
+         "batch_and_one": list(range(70, 79)), "all": list(range(128))}
 
 
 @pytest.mark.parametrize("B", [2, 257])
