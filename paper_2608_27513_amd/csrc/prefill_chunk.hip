@@ -78,6 +78,7 @@
 // heads, 64 tokens: 805 -> 316 us; KDA, B = 32, 250 tokens: 498 -> 265 us; GDN,
 // two requests of 1024 tokens: 728 -> 134 us; 2 tokens at B = 256: 154 -> 139 us
 // (GDN), 167 -> 164 us (KDA).
+#include <atomic>
 #include <cfloat>
 #include <cstdint>
 
@@ -1335,15 +1336,27 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
                                    s_g);
 }
 
-// A CU holds one eight-wave workgroup or three of four waves. While every tile
-// has a CU to itself, a wave's own instruction rate is what counts (one in 5
-// cycles, whatever else the CU could do), so staging beside the chunks pays;
-// with more tiles the second round it costs does not. One to eight requests of
-// 32 heads (up to 256 tiles), 1024 tokens: GDN 181-186 -> 135-137 us, KDA
-// 402-404 -> 280-283; 8 tokens: 10.3-11.4 -> 10.3-10.5 and 12.2-13.3 -> 11.4-12.5
-// (the first chunks are staged while the tile arrives). Twelve requests (384
-// tiles), 250 tokens: GDN 71 -> 84, KDA 136 -> 152.
-bool split_waves(int64_t tiles) { return tiles <= 256; }
+// A CU (256 of them, fewer in a partition of the device) holds one eight-wave
+// workgroup or three of four waves. While every tile has a CU to itself, a
+// wave's own instruction rate is what counts (one in 5 cycles, whatever else the
+// CU could do), so staging beside the chunks pays; with more tiles the second
+// round it costs does not. One to eight requests of 32 heads (up to 256 tiles),
+// 1024 tokens: GDN 181-186 -> 135-137 us, KDA 402-404 -> 280-283; 8 tokens:
+// 10.3-11.4 -> 10.3-10.5 and 12.2-13.3 -> 11.4-12.5 (the first chunks are staged
+// while the tile arrives). Twelve requests (384 tiles), 250 tokens: GDN 71 ->
+// 84, KDA 136 -> 152.
+bool split_waves(int64_t tiles) {
+  static std::atomic<int> cus_of[16];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 16) return false;
+  int cus = cus_of[dev].load(std::memory_order_relaxed);
+  if (cus == 0) {
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      return false;
+    cus_of[dev].store(cus, std::memory_order_relaxed);
+  }
+  return tiles <= cus;
+}
 
 template <int KIND, bool KDA>
 void launch_kind(const PrefillParams& p, int B, hipStream_t stream) {
