@@ -456,3 +456,38 @@ def test_prefill_scale_of_state_and_values(kda, power, B):
     err, s_err = rel_l2(o_gpu, o_ref), rel_l2(state, ref.buf.view(np.float32))
     _say(f"  kda={kda} 2^{power} B={B}: o rel-L2 {err:.2e} state rel-L2 {s_err:.2e}")
     assert err <= 1e-6 and s_err <= 1e-6
+
+
+@pytest.mark.parametrize("kda", [False, True])
+@pytest.mark.parametrize("kind", ["fp32", "mixed"])
+@pytest.mark.parametrize("HV,T", [(131071, 49), (131080, 3)])
+def test_prefill_as_many_heads_as_the_chunked_kernel_addresses(HV, T, kind, kda):
+    """With 131 071 value heads the 64 token rows of a head span what the
+    chunked kernel's 32-bit offsets reach; with more, d = 128 runs in the
+    generic kernel. The heads at both ends against a pool of them alone, over
+    two calls (the second from the stored state of the first)."""
+    d, n = 128, 8
+    if kind == "fp32":
+        layout, tol = D.damp_layout_init(d, d, 0, D.DAMP_STATE_FP32), 1e-6
+    else:  # one code of 255 apart in up to 1e-4 of the values (measured: 5e-5)
+        layout, tol = D.damp_layout_init(d, d, 16), 1e-4
+    gen = torch.Generator(device="cuda").manual_seed(841)
+    slots = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ends = torch.cat([torch.arange(n), torch.arange(HV - n, HV)]).cuda()
+    pools = [D.Pool(layout, 1, 1, h) for h in (HV, 2 * n)]
+    for pool in pools:
+        D.damp_pool_reset_slots(pool, 0, slots)
+    fn = D.damp_state_prefill_kda if kda else D.damp_state_prefill_gdn
+    for _ in range(2):
+        x = {m: torch.randn((1, T, HV, d), generator=gen, device="cuda") for m in "qkv"}
+        for m in "qk":
+            x[m] /= x[m].norm(dim=-1, keepdim=True)
+        x["g"] = -torch.rand((1, T, HV, d) if kda else (1, T, HV), generator=gen, device="cuda")
+        x["beta"] = torch.rand((1, T, HV), generator=gen, device="cuda")
+        o = []
+        for pool, pick in zip(pools, (lambda t: t, lambda t: t[:, :, ends])):
+            a = {m: pick(t).to(torch.bfloat16).contiguous() for m, t in x.items()}
+            o.append(fn(pool, 0, slots, a["q"], a["k"], a["v"], a["g"], a["beta"]))
+        assert rel_l2(o[0][:, :, ends].cpu(), o[1].cpu()) <= tol
+    S = [D.damp_state_unpack(pool, 0, slots)[0] for pool in pools]
+    assert rel_l2(S[0][ends].cpu(), S[1].cpu()) <= tol
