@@ -491,3 +491,51 @@ def test_prefill_as_many_heads_as_the_chunked_kernel_addresses(HV, T, kind, kda)
         assert rel_l2(o[0][:, :, ends].cpu(), o[1].cpu()) <= tol
     S = [D.damp_state_unpack(pool, 0, slots)[0] for pool in pools]
     assert rel_l2(S[0][ends].cpu(), S[1].cpu()) <= tol
+
+
+PREFILL_FORMATS = {"fp32": (orc.KIND_FP32, 0, None), "default": (orc.KIND_MIXED, 16, None),
+                   "default_k0": (orc.KIND_MIXED, 0, None),
+                   "int8_h32": (orc.KIND_MIXED, 16, orc.FMT_PAPER),
+                   "int8_g32": (orc.KIND_MIXED, 16, orc.FMT_PAPER_PLAIN),
+                   "int4": (orc.KIND_MIXED, 16, orc.FMT_INT4),
+                   "int4_h32": (orc.KIND_MIXED, 16, orc.FMT_INT4_H32),
+                   "fp8": (orc.KIND_MIXED, 16, orc.FMT_FP8),
+                   "nvfp4": (orc.KIND_MIXED, 16, orc.FMT_NVFP4)}
+
+
+@pytest.mark.parametrize("B", [5, 131])
+@pytest.mark.parametrize("kda", [False, True])
+@pytest.mark.parametrize("name", list(PREFILL_FORMATS))
+def test_prefill_formats_at_both_launch_shapes(name, kda, B):
+    """d = 128 in every storage format, with up to 256 tiles (staging waves of
+    their own) and with more (four waves, the tile's transit in the memory of
+    the staged chunks): a partial last chunk, permuted channels, scattered
+    slots, a padded and an out-of-range request, and slots that no request
+    names, which keep their bytes."""
+    kind, k_hi, fmt = PREFILL_FORMATS[name]
+    d, HV, T, n_slots = 128, 2, 37, B + 3
+    HK = HV if kda else 1
+    seed = 851 + B
+    _say(f"prefill {name} kda={kda} B={B}")
+    slots = inputs.slot_order(seed, n_slots, B)
+    slots[1], slots[3] = -1, n_slots
+    live = (slots >= 0) & (slots < n_slots)
+    perm = inputs.random_perms(seed, HV, d)
+    ref = orc.Pool(kind, d, d, k_hi, 1, n_slots, HV, fmt=fmt)
+    # the states of every slot, those of no request among them
+    orc.pack(ref, 0, np.arange(n_slots), inputs.synthetic_states(seed, n_slots, HV, d), perm)
+    before = ref.buf.copy()
+    gpool = gpu_pool_from(ref, D)
+    inp = inputs.as_prefill(inputs.decode_inputs(seed, T, B, HK, HV, d, kda=kda))
+    o_gpu, o_ref = _run(kda, ref, gpool, slots, inp, perm, scale=0.5)
+    host = gpool.buffer.cpu().numpy()
+    err = rel_l2(o_gpu, o_ref)
+    stats = compare_tiles(host, ref, f"prefill {name}", s16_exact_min=0.99)
+    _say(f"  o rel-L2 {err:.2e}  {stats}")
+    # identical starting bytes and fp32 from there: only the order of the sums
+    assert err <= 1e-6
+    assert (o_gpu[~live] == 0).all()
+    idle = np.setdiff1d(np.arange(n_slots), slots[live])
+    st = ref.slot_stride
+    for s in idle:
+        assert np.array_equal(host[s * st:(s + 1) * st], before[s * st:(s + 1) * st])
