@@ -44,8 +44,8 @@ CASES = [
     (128, False, 2, 4, 2, 8, 16, orc.KIND_MIXED, orc.FMT_PAPER),
     (128, True, 2, 2, 2, 1, 32, orc.KIND_MIXED, None),
     (128, False, 2, 2, 2, 12, 0, orc.KIND_FP32, None),
-    # d = 128 runs in blocks of 8 tokens: a partial last block; GDN's decay
-    # product leaving [2^-40, 2^40] (renormalized); the other formats
+    # d = 128 runs in chunks of 16 tokens: one token past a chunk; several
+    # chunks, with decays whose product vanishes; the other formats
     (128, True, 2, 2, 2, 17, 12, orc.KIND_MIXED, None),
     (128, False, 2, 2, 2, 48, 16, orc.KIND_MIXED, None),
     (128, False, 2, 4, 3, 24, 16, orc.KIND_MIXED, orc.FMT_INT4_H32),
@@ -101,12 +101,12 @@ def test_prefill_padded_requests_and_bf16_output(d, T):
 
 
 def test_prefill_kda_blocks_with_vanishing_decay():
-    """KDA at d = 128 defers each row's decay over a block of 8 tokens unless
-    some row's running product leaves [2^-60, 2^60]; here the middle of three
-    blocks holds a channel decaying by e^-12 per token (product e^-96) and one
-    token with a zero decay (g = -inf), so the per-token and the deferred
-    blocks alternate within one chunk."""
-    d, HK, HV, B, T, k_hi = 128, 2, 2, 2, 24, 16
+    """KDA at d = 128 refers a chunk of 16 tokens to its middle token unless a
+    channel's product on either side of it leaves [2^-80, 2^80]; here the
+    second of four chunks holds a channel decaying by e^-12 per token (product
+    e^-96 over eight) and one token with a zero decay (g = -inf), between
+    chunks without such channels."""
+    d, HK, HV, B, T, k_hi = 128, 2, 2, 2, 56, 16
     seed = 733
     slots = inputs.slot_order(seed, B + 2, B)
     perm = inputs.random_perms(seed, HV, d)
@@ -115,8 +115,8 @@ def test_prefill_kda_blocks_with_vanishing_decay():
     gpool = gpu_pool_from(ref, D)
     inp = inputs.as_prefill(inputs.decode_inputs(seed, T, B, HK, HV, d, kda=True))
     g = inp["g"].copy()  # bf16 bits [B, T, HV, d]
-    g[0, 8:16, 0, 5] = inputs.to_bf16_bits(np.float32(-12.0))[0]
-    g[1, 12, 1, 70] = inputs.to_bf16_bits(np.float32(-np.inf))[0]
+    g[0, 24:32, 0, 5] = inputs.to_bf16_bits(np.float32(-12.0))[0]
+    g[1, 28, 1, 70] = inputs.to_bf16_bits(np.float32(-np.inf))[0]
     inp["g"] = g
     o_gpu, o_ref = _run(True, ref, gpool, slots, inp, perm)
     err = rel_l2(o_gpu, o_ref)
@@ -127,12 +127,12 @@ def test_prefill_kda_blocks_with_vanishing_decay():
 
 
 def test_prefill_gdn_vanishing_and_zero_decay():
-    """GDN at d = 128 defers the scalar decay as S = gamma P with gamma kept in
-    [2^-40, 2^40]; a token whose decay would take gamma out of that range is
-    applied to P directly. Here: a zero decay (g = -inf), decays below the
-    smallest normal fp32 number (g = -100, -90), and a run of e^-5 decays
-    whose product leaves the range in the middle of a block."""
-    d, HK, HV, B, T, k_hi = 128, 1, 2, 2, 24, 16
+    """GDN at d = 128 takes the decays of a chunk of 16 tokens as running
+    products, which may vanish. Here, in the second of four chunks: a zero
+    decay (g = -inf), decays below the smallest normal fp32 number (g = -100,
+    -90), and a run of e^-5 decays; and a zero decay at the first token of the
+    third."""
+    d, HK, HV, B, T, k_hi = 128, 1, 2, 2, 56, 16
     seed = 741
     slots = inputs.slot_order(seed, B + 2, B)
     perm = inputs.random_perms(seed, HV, d)
@@ -142,11 +142,11 @@ def test_prefill_gdn_vanishing_and_zero_decay():
     inp = inputs.as_prefill(inputs.decode_inputs(seed, T, B, HK, HV, d))
     g = inp["g"].copy()  # bf16 bits [B, T, HV]
     bits = lambda x: inputs.to_bf16_bits(np.float32(x))[0]
-    g[0, 3, 0] = bits(-np.inf)
-    g[0, 10, 0] = bits(-100.0)
-    g[1, 5:15, 1] = bits(-5.0)
-    g[1, 20, 1] = bits(-90.0)
-    g[0, 17, 1] = bits(-np.inf)
+    g[0, 19, 0] = bits(-np.inf)
+    g[0, 26, 0] = bits(-100.0)
+    g[1, 18:28, 1] = bits(-5.0)
+    g[1, 30, 1] = bits(-90.0)
+    g[0, 32, 1] = bits(-np.inf)
     inp["g"] = g
     o_gpu, o_ref = _run(False, ref, gpool, slots, inp, perm)
     assert np.isfinite(o_gpu).all()
@@ -159,7 +159,7 @@ def test_prefill_gdn_vanishing_and_zero_decay():
 
 def test_calibrate_sequence_gdn_vanishing_decay():
     """The calibration trajectory of GDN at d = 128 runs through the same
-    deferred-decay prefill kernel: zero and sub-normal decays (g = -inf,
+    chunked prefill kernel, a window of one stride at a time: zero and sub-normal decays (g = -inf,
     -100) between the sampled tokens keep the FP32 trajectory finite and
     equal to the oracle's."""
     d, H, HK, B, T = 128, 2, 1, 2, 24
@@ -282,8 +282,7 @@ def test_prefill_nonfinite_input_leaves_earlier_tokens(kda, what, B):
 @pytest.mark.parametrize("kda", [False, True])
 def test_prefill_vanishing_decays_with_many_tiles(kda):
     """Zero decays and decays whose products leave the range of the chunk form,
-    in a batch of more than 256 tiles: single-token chunks between chunks in
-    matrix form, every request against the oracle."""
+    in a batch of more than 256 tiles, every request against the oracle."""
     d, HK, HV, B, T = 128, 1, 1, 260, 50
     seed = 797
     ref = orc.Pool(orc.KIND_FP32, d, d, 0, 1, B, HV)
