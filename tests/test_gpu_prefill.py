@@ -198,7 +198,9 @@ def test_prefill_chunk_edges(kda, T, B):
     the edges of the four-row groups, of a chunk and of a staging block, and a
     partial last chunk; with up to 256 tiles staged by waves of their own, with
     more (B = 129, two heads) by the waves that run them. FP32 state, so o and
-    the state carry fp32 rounding only (the bar of the FP32 path)."""
+    the state carry fp32 rounding only: 7e-8 to 3.4e-7 measured, and 2.2e-6 to
+    1.1e-5 with the third part of the state's splits left out, so a bar of 1e-6
+    pins that part."""
     d, HK, HV = 128, 2 if kda else 1, 2
     seed = 760 + T
     slots = inputs.slot_order(seed, B + 1, B)
@@ -211,7 +213,7 @@ def test_prefill_chunk_edges(kda, T, B):
     state = gpool.buffer.cpu().numpy().view(np.float32)
     err, s_err = rel_l2(o_gpu, o_ref), rel_l2(state, ref.buf.view(np.float32))
     _say(f"  T={T} kda={kda} o rel-L2 {err:.2e} state rel-L2 {s_err:.2e}")
-    assert err <= 1e-5 and s_err <= 1e-5
+    assert err <= 1e-6 and s_err <= 1e-6
 
 
 @pytest.mark.parametrize("kda", [False, True])
@@ -302,7 +304,7 @@ def test_prefill_vanishing_decays_with_many_tiles(kda):
     o_gpu, o_ref = _run(kda, ref, gpool, np.arange(B), inp, None)
     state = gpool.buffer.cpu().numpy().view(np.float32)
     assert np.isfinite(o_gpu).all() and np.isfinite(state).all()
-    assert rel_l2(o_gpu, o_ref) <= 1e-5 and rel_l2(state, ref.buf.view(np.float32)) <= 1e-5
+    assert rel_l2(o_gpu, o_ref) <= 1e-6 and rel_l2(state, ref.buf.view(np.float32)) <= 1e-6
 
 
 def _fp32_case(kda, B, HV, T, seed, states=None, HK=None):
