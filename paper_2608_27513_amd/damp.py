@@ -127,9 +127,15 @@ def _stream(stream=None):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+# the handle of a device's current stream; torch makes no Stream object for it
+# in its private form, which is taken where this torch has it
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _raw_stream(stream=None) -> int:
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        return _current_raw_stream(torch.cuda.current_device())
     return stream.cuda_stream
 
 

@@ -398,3 +398,22 @@ def test_operand_check_refuses_what_is_no_device_tensor(t):
     is not a device tensor."""
     with pytest.raises(ValueError, match="x must be a CUDA"):
         D._at(t, torch.float32, "x", (2,))
+
+
+def test_current_stream_without_the_private_accessor(monkeypatch):
+    """A torch without the private accessor of the current stream's handle
+    takes the public one."""
+    import importlib.util
+
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    spec = importlib.util.spec_from_file_location("damp_again", D.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device: Stream if device == 3 else None)
+    assert again._raw_stream() == 0x1234
+    assert again._raw_stream(Stream) == 0x1234
