@@ -39,9 +39,9 @@
 // references, where no inverse is needed: k_t G_t with S0, k_s L_{15,s} with U,
 // and S0 takes G_15 between the two. A chunk runs token by token if a product
 // passes 2^80, if its k, q, v or beta reaches 2^32, 2^32, 2^32, 2^16 or a column
-// of its v is below 2^-24 but not zero: so k^ and k^ U stay finite, and the
-// third parts of S0' and R stay above the smallest normal number, below which
-// the products drop them. Nor may |A| pass 2^7 (it is looked at where k, beta or
+// of its v or a pair of channels of its q is below 2^-24 but not zero: so k^ and
+// k^ U stay finite, and the third parts of S0', R and q~ stay above the smallest
+// normal number, below which the products drop them. Nor may |A| pass 2^7 (it is looked at where k, beta or
 // a decay is above one): so T, whose entries reach (1 + |A|)^14, stays finite.
 // One channel at g = -9 in every head, FP32 state, token by token and in this
 // form: B = 32, 250 tokens 835 -> 372 us (334 with none), B = 8, 1024 tokens
@@ -227,6 +227,10 @@ struct MaxBits {
   __device__ __forceinline__ uint32_t bits() const { return pair.x > pair.y ? pair.x : pair.y; }
 };
 constexpr uint32_t bf16_pow2(int e) { return static_cast<uint32_t>(127 + e) << 7; }
+// Of the bits of a bf16 magnitude: not zero, and outside [2^-24, 2^32).
+__device__ __forceinline__ bool out_of_scale(uint32_t bits) {
+  return bits != 0u && bits - bf16_pow2(-24) >= bf16_pow2(32) - bf16_pow2(-24);
+}
 
 // `n` rows of `bytes` bytes, `step` bytes apart, as a raw buffer that ends with
 // the last row: reads past it return zero and writes are dropped.
@@ -261,7 +265,7 @@ struct alignas(16) ChunkLds<true> {
   float tm[32][kC];
   alignas(16) float pre[kD], fin[kD];
   float beta[kC];
-  int32_t flag[4], vflag[4];  // form by staging wave; kTokens by wave, its columns of v
+  int32_t flag[4];  // what each staging wave found
   // steep channels, by staging wave: a bit per pair of channels (even, odd
   // channels); some of them at its tokens (k, q, a); their sums for A and B
   // between its tokens s and t, at 8 s + t; and for all, the factors that take
@@ -505,8 +509,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
   auto form_of = [&](const typename P::Chunk& ck) __attribute__((always_inline)) -> int {
     int f;
     if constexpr (KDA)
-      f = ck.flag[0] | ck.flag[1] | ck.flag[2] | ck.flag[3] | ck.vflag[0] | ck.vflag[1] |
-          ck.vflag[2] | ck.vflag[3];
+      f = ck.flag[0] | ck.flag[1] | ck.flag[2] | ck.flag[3];
     else
       f = ck.flag;
     return __builtin_amdgcn_readfirstlane(f);
@@ -647,7 +650,13 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
       }
       const float beta = bf16_to_f32(static_cast<uint16_t>(in.beta));
       const uint32_t kbits = kmax.bits();
-      bool bad = qmax.bits() >= bf16_pow2(32) || !(whole[0] <= FLT_MAX) || !(whole[1] <= FLT_MAX);
+      uint32_t vmax = 0u;  // of this wave's columns
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t av = in.v[KDA ? e : 0] & 0x7fffu;
+        vmax = av > vmax ? av : vmax;
+      }
+      bool bad = out_of_scale(qmax.bits()) || out_of_scale(vmax) || !(whole[0] <= FLT_MAX) || !(whole[1] <= FLT_MAX);
       int form = 0;
       // |k|, |beta| and the decays at most 1: |A| <= 128 = kKeysMax
       const bool wide = kbits > bf16_pow2(0) || !(fabsf(beta) <= 1.0f) || amax > 1.0f;
@@ -669,15 +678,6 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         form |= kSteep;
       }
       if (lane == 0) ck.flag[wave] = form;
-      uint32_t vmax = 0u;  // bits of the largest |v| of the lane's tokens
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint32_t av = in.v[KDA ? e : 0] & 0x7fffu;
-        vmax = av > vmax ? av : vmax;
-      }
-      const bool v_out = vmax != 0u && vmax - bf16_pow2(-24) >= bf16_pow2(32) - bf16_pow2(-24);
-      const bool v_flagged = __builtin_amdgcn_ballot_w64(v_out) != 0;
-      if (lane == 0) ck.vflag[wave] = v_flagged ? kTokens : 0;
       if (wave == 0 && lane < kC) ck.beta[lane] = beta;
       // the lanes of a channel's far tokens hold the product of all eight
       if ((half == 0) == (ph == 0))

@@ -540,3 +540,22 @@ def test_prefill_formats_at_both_launch_shapes(name, kda, B):
     st = ref.slot_stride
     for s in idle:
         assert np.array_equal(host[s * st:(s + 1) * st], before[s * st:(s + 1) * st])
+
+
+@pytest.mark.parametrize("B", [2, 129])
+@pytest.mark.parametrize("power", [28, -20, -60, -90])
+@pytest.mark.parametrize("kda", [False, True])
+def test_prefill_scale_of_queries(kda, power, B):
+    """o is linear in q: its scale costs no precision, KDA's decays as in the
+    test of the state's scale."""
+    HV, T, seed = 2, 40, 861
+    ref, gpool, inp = _fp32_case(kda, B, HV, T, seed, inputs.synthetic_states(seed, B, HV, 128))
+    inp["q"] = _scale_bf16(inp["q"], 2.0 ** power)
+    if kda:
+        g = inp["g"].copy()
+        g[..., 3::16] = _bits(-79 * np.log(2.0) / 8)
+        inp["g"] = g
+    o_gpu, o_ref = _run(kda, ref, gpool, np.arange(B), inp, None)
+    err = rel_l2(o_gpu, o_ref)
+    _say(f"  kda={kda} 2^{power} B={B}: o rel-L2 {err:.2e}")
+    assert err <= 1e-6
