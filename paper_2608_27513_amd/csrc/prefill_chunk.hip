@@ -41,12 +41,13 @@
 // passes 2^80, if its k, q, v or beta reaches 2^32, 2^32, 2^32, 2^16 or a column
 // of its v or a pair of channels of its q is below 2^-24 but not zero: so k^ and
 // k^ U stay finite, and the third parts of S0', R and q~ stay above the smallest
-// normal number, below which the products drop them. Nor may |A| pass 2^7 (it is looked at where k, beta or
-// a decay is above one): so T, whose entries reach (1 + |A|)^14, stays finite.
+// normal number, below which the products drop them. Nor may |A| pass 2^7 (it is
+// looked at where k, beta or a decay is above one): so T, whose entries reach
+// (1 + |A|)^14, stays finite.
 // One channel at g = -9 in every head, FP32 state, token by token and in this
 // form: B = 32, 250 tokens 835 -> 372 us (334 with none), B = 8, 1024 tokens
-// 1433 -> 465 (307), B = 256, 64 tokens 1530 -> 728 (667). Every channel: 785 ->
-// 575, 1433 -> 839, 1536 -> 1077.
+// 1433 -> 421 (307), B = 256, 64 tokens 1530 -> 706 (667). Every channel: 785 ->
+// 565, 1433 -> 843, 1536 -> 1002.
 //
 // Mapping. A workgroup of four waves owns one (request, value head) tile;
 // wave w holds columns 32 w .. 32 w + 31 of the state for all 128 channels, in
@@ -67,16 +68,18 @@
 // three-way splits are half. A wave alone issues one in 5 cycles, and a matrix
 // instruction keeps the SIMD's vector unit from others' use for about 22 of
 // its 32 cycles, so the kernel is held to 168 registers and 51 200 bytes of
-// LDS: three workgroups a CU. While there are no more tiles than CUs, a
-// workgroup has four more waves that stage the next chunks meanwhile (SPLIT).
-// A register that spills costs more than it looks
-// (its reload waits for every load and store before it: 336 -> 440 us with
-// some ten in the loop), hence opaque() and the scheduling barriers. Chunks of
-// 16: the products within a chunk and T grow with its square.
+// LDS: three workgroups a CU. KDA's four-wave form waits as much as it issues
+// (39% of its wave cycles): it stages a single chunk, behind barriers at which
+// only some waves have work. While there are no more tiles than CUs, a workgroup
+// has four more waves that stage the next chunks meanwhile (SPLIT). A register
+// that spills costs more than it looks (its reload waits for every load and
+// store before it: 336 -> 440 us with some ten in the loop), hence opaque() and
+// the scheduling barriers. Chunks of 16: the products within a chunk and T grow
+// with its square.
 // Measured against the token-by-token fp32 kernel before it (two FMAs per
 // value and token for the read-outs, one for the update), GDN, B = 256, 32
-// heads, 64 tokens: 805 -> 316 us; KDA, B = 32, 250 tokens: 498 -> 265 us; GDN,
-// two requests of 1024 tokens: 728 -> 134 us; 2 tokens at B = 256: 154 -> 139 us
+// heads, 64 tokens: 805 -> 309 us; KDA, B = 32, 250 tokens: 498 -> 264 us; GDN,
+// two requests of 1024 tokens: 722 -> 134 us; 2 tokens at B = 256: 154 -> 139 us
 // (GDN), 167 -> 164 us (KDA).
 #include <atomic>
 #include <cfloat>
@@ -517,7 +520,8 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
   // KDA: the same once the products are there
   auto with_grows = [&](const typename P::Chunk& ck, int form) __attribute__((always_inline)) -> int {
     if constexpr (KDA) {
-      if (__builtin_expect((form & kKeys) != 0, 0)) form |= __builtin_amdgcn_readfirstlane(ck.grows);
+      if (__builtin_expect((form & kKeys) != 0, 0))
+        form |= __builtin_amdgcn_readfirstlane(ck.grows);
     }
     return form;
   };
@@ -656,7 +660,8 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 2 : 3) void prefill_chun
         const uint32_t av = in.v[KDA ? e : 0] & 0x7fffu;
         vmax = av > vmax ? av : vmax;
       }
-      bool bad = out_of_scale(qmax.bits()) || out_of_scale(vmax) || !(whole[0] <= FLT_MAX) || !(whole[1] <= FLT_MAX);
+      bool bad = out_of_scale(qmax.bits()) || out_of_scale(vmax) || !(whole[0] <= FLT_MAX) ||
+                 !(whole[1] <= FLT_MAX);
       int form = 0;
       // |k|, |beta| and the decays at most 1: |A| <= 128 = kKeysMax
       const bool wide = kbits > bf16_pow2(0) || !(fabsf(beta) <= 1.0f) || amax > 1.0f;

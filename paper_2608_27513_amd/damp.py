@@ -241,7 +241,7 @@ def damp_pool_reset_slots(pool: Pool, layer: int, slots: torch.Tensor, stream=No
 
 def _update_args(kda: bool, pool: Pool, layer: int, slot_idx, q, k, v, g, beta, perm, scale,
                  o, stream):
-    """Checks the operands and returns (C function, argument tuple)."""
+    """Checks the operands and returns (C function, arguments)."""
     d = pool.layout.d_k
     HV = pool.num_v_heads
     _dev(slot_idx, torch.int32, "slot_idx")
