@@ -559,3 +559,27 @@ def test_prefill_scale_of_queries(kda, power, B):
     err = rel_l2(o_gpu, o_ref)
     _say(f"  kda={kda} 2^{power} B={B}: o rel-L2 {err:.2e}")
     assert err <= 1e-6
+
+
+@pytest.mark.parametrize("B", [2, 257])
+@pytest.mark.parametrize("norm,T", [(1.0, 40), (64.0, 6)])
+def test_prefill_kda_wide_operands_beside_steep_channels(norm, T, B):
+    """beta in (0, 2) and factors above one, where a chunk's |A| is looked at:
+    within its bound (keys of norm 1) the chunk stays in matrix form, beyond it
+    (norm 64) it runs token by token, with steep channels staged in it either
+    way. Six tokens of the larger keys grow the state to about 1e19, and its
+    rounding with it."""
+    HV, seed = 1, 871
+    ref, gpool, inp = _fp32_case(True, B, HV, T, seed, inputs.synthetic_states(seed, B, HV, 128))
+    inp["k"] = _scale_bf16(inp["k"], norm)
+    inp["beta"] = _scale_bf16(inp["beta"], 2.0)
+    g = inp["g"].copy()
+    g[..., 11] = _bits(0.125)
+    g[..., 40:43] = _bits(-20.0)
+    inp["g"] = g
+    o_gpu, o_ref = _run(True, ref, gpool, np.arange(B), inp, None)
+    state = gpool.buffer.cpu().numpy().view(np.float32)
+    err, s_err = rel_l2(o_gpu, o_ref), rel_l2(state, ref.buf.view(np.float32))
+    _say(f"  norm {norm} B={B}: o rel-L2 {err:.2e} state rel-L2 {s_err:.2e}")
+    tol = 1e-6 if norm == 1.0 else 1e-4
+    assert np.isfinite(o_ref).all() and err <= tol and s_err <= tol
